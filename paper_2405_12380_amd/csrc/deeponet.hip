@@ -144,6 +144,13 @@ static helm_status trunk_eval(don_s* net, helm_op_s* op, T* out, hipStream_t st)
   constexpr bool wide = sizeof(T) == sizeof(double);
   const size_t n = op->nn;
   const int L = (int)net->tw.size() - 1;
+  if (trunk_fused_fits(L, net->tw.data())) {
+    const std::vector<void*>& Wf = wide ? net->tW : net->tW64;
+    const std::vector<void*>& Bf = wide ? net->tB : net->tB64;
+    trunk_fused<T>(op->dim, op->n, L, net->tw.data(), (const double* const*)Wf.data(), (const double* const*)Bf.data(),
+                   map_act(net->act), out, st);
+    return launch_check("trunk");
+  }
   int maxw = 1;
   for (int w : net->tw) maxw = w > maxw ? w : maxw;
   const size_t chunk = n < (size_t)262144 ? n : (size_t)262144;

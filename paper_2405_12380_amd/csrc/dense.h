@@ -15,6 +15,15 @@ enum { ACT_NONE = -1, ACT_TANH = 0, ACT_RELU = 1, ACT_LEAKY = 2 };
 template <typename T>
 void coord_layer(int dim, const int n[3], size_t row0, size_t nrows, const T* W, const T* b, int N, int act, T* out,
                  hipStream_t st);
+// out = the trunk matrix T (nn x w[L], row-major) of the grid's nodes: all L layers
+// (W[l]: w[l] x w[l + 1], hidden activation act, last layer linear) in one
+// launch, fp64 arithmetic, rounded once to T as stored.  Only for widths that
+// trunk_fused_fits accepts.
+constexpr int TRUNK_MAXL = 8;
+bool trunk_fused_fits(int L, const int* w);
+template <typename T>
+void trunk_fused(int dim, const int n[3], int L, const int* w, const double* const* W, const double* const* b, int act,
+                 T* out, hipStream_t st);
 // C = act(A W + bias) (fp64 MFMA; instantiated for double); bias may be NULL;
 // act = ACT_NONE for linear
 template <typename T>

@@ -4,39 +4,13 @@
 // one-workgroup factorizations of small matrices (Cholesky with column
 // dropping, triangular inverse, Gauss-Jordan inverse of the complex coarse
 // matrix).
-//
-// MFMA: v_mfma_f64_16x16x4f64.  Lane l supplies A[l % 16][l / 16] and
-// B[l / 16][l % 16] of a 16x4 by 4x16 product; its four accumulator registers
-// hold rows (l / 16) + 4 i of column l % 16.  Both dtypes evaluate the network
-// layers in fp64 (a C64 network's fp32 weights widened exactly).
+// Both dtypes evaluate the network layers in fp64 (a C64 network's fp32
+// weights widened exactly).
 #include "common.h"
-#include "dense.h"
+#include "dense_dev.h"
 #include "prof.h"
 
 namespace helm {
-
-typedef double d4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ d4 mfma16(double a, double b, d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ int acc_row(int lane, int i) { return (lane >> 4) + 4 * i; }
-
-// tanh for the fp64 layers from expm1: t = e^{2|x|} - 1, tanh|x| = t / (t + 2),
-// sign restored (no cancellation near 0; within 5e-16 of the library tanh and
-// about 3x cheaper per element, which matters in the trunk GEMM epilogue)
-__device__ __forceinline__ double tanh_fast(double x) {
-  const double t = expm1(2.0 * fabs(x));
-  return copysign(t / (t + 2.0), x);
-}
-
-template <typename T>
-__device__ __forceinline__ T activate(T x, int act) {
-  if (act == ACT_TANH) return tanh_fast(x);
-  if (act == ACT_RELU) return x > T(0) ? x : T(0);
-  if (act == ACT_LEAKY) return x > T(0) ? x : T(0.01) * x;
-  return x;
-}
 
 // ---- trunk input layer: h = act(x W + b) at grid-node coordinates --------------
 // Workgroup b takes rows [b rpb, (b + 1) rpb) of the output, threads its
