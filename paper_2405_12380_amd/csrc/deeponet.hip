@@ -19,7 +19,7 @@
 #include <vector>
 
 #include "common.h"
-#include "dense.h"
+#include "dense_dev.h"
 #include "internal.h"
 #include "lib.h"
 
@@ -69,52 +69,250 @@ __global__ void k_branch_in_identity(size_t n, const cplx_t<S>* __restrict__ r, 
   }
 }
 
+// r sampled at branch-grid node j by multilinear interpolation (zero ghosts)
+struct SampleGrid {
+  int dim, n[3], m[3];  // op grid, branch grid
+};
+template <typename S>
+__device__ __forceinline__ double2 sample_node(const SampleGrid& g, const cplx_t<S>* __restrict__ r, size_t j) {
+  const int jj[3] = {(int)(j % g.m[0]), (int)((j / g.m[0]) % g.m[1]), (int)(j / ((size_t)g.m[0] * g.m[1]))};
+  int i0[3];
+  double w[3];
+  for (int a = 0; a < 3; ++a) {
+    if (a < g.dim && g.m[a] != g.n[a]) {
+      const double xt = (double)(jj[a] + 1) / (double)(g.m[a] + 1);
+      const double t = __dmul_rn(xt, (double)(g.n[a] + 1)) - 1.0;
+      i0[a] = (int)floor(t);
+      w[a] = t - i0[a];
+    } else {
+      i0[a] = jj[a];
+      w[a] = 0.0;
+    }
+  }
+  double2 acc = czero();
+  const int nc = 1 << g.dim;
+  for (int cidx = 0; cidx < nc; ++cidx) {
+    double wt = 1.0;
+    int idx[3] = {0, 0, 0};
+    bool inside = true;
+    for (int a = 0; a < 3; ++a) {
+      const int bit = a < g.dim ? (cidx >> a) & 1 : 0;
+      idx[a] = i0[a] + bit;
+      wt *= bit ? w[a] : 1.0 - w[a];
+      if (a < g.dim && (idx[a] < 0 || idx[a] >= g.n[a])) inside = false;
+    }
+    if (!inside || wt == 0.0) continue;
+    const size_t p = (size_t)idx[0] + (size_t)g.n[0] * ((size_t)idx[1] + (size_t)g.n[1] * idx[2]);
+    const double2 v = ldc(r, p);
+    acc.x += wt * v.x;
+    acc.y += wt * v.y;
+  }
+  return acc;
+}
+
 // branch input by multilinear interpolation onto the branch grid (zero ghosts):
 // x[0][j] = sample(Re r / s), x[0][m + j] = sample(Im r / s), x[0][2m] = k
 template <typename T, typename S>
-__global__ void k_branch_in_sample(int dim, int nx, int ny, int nz, int mx, int my, int mz,
-                                   const cplx_t<S>* __restrict__ r, const double* __restrict__ sv, int split_input,
-                                   int k_input, double k, T* __restrict__ x) {
-  const size_t m = (size_t)mx * my * mz;
+__global__ void k_branch_in_sample(SampleGrid g, const cplx_t<S>* __restrict__ r, const double* __restrict__ sv,
+                                   int split_input, int k_input, double k, T* __restrict__ x) {
+  const size_t m = (size_t)g.m[0] * g.m[1] * g.m[2];
   const double inv = sv[1];
-  const int ns[3] = {nx, ny, nz}, mt[3] = {mx, my, mz};
   for (size_t j = blockIdx.x * (size_t)blockDim.x + threadIdx.x; j < m; j += (size_t)gridDim.x * blockDim.x) {
-    const int jj[3] = {(int)(j % mx), (int)((j / mx) % my), (int)(j / ((size_t)mx * my))};
-    int i0[3];
-    double w[3];
-    for (int a = 0; a < 3; ++a) {
-      if (a < dim && mt[a] != ns[a]) {
-        const double xt = (double)(jj[a] + 1) / (double)(mt[a] + 1);
-        const double t = __dmul_rn(xt, (double)(ns[a] + 1)) - 1.0;
-        i0[a] = (int)floor(t);
-        w[a] = t - i0[a];
-      } else {
-        i0[a] = jj[a];
-        w[a] = 0.0;
-      }
-    }
-    double2 acc = czero();
-    const int nc = 1 << dim;
-    for (int cidx = 0; cidx < nc; ++cidx) {
-      double wt = 1.0;
-      int idx[3] = {0, 0, 0};
-      bool inside = true;
-      for (int a = 0; a < 3; ++a) {
-        const int bit = a < dim ? (cidx >> a) & 1 : 0;
-        idx[a] = i0[a] + bit;
-        wt *= bit ? w[a] : 1.0 - w[a];
-        if (a < dim && (idx[a] < 0 || idx[a] >= ns[a])) inside = false;
-      }
-      if (!inside || wt == 0.0) continue;
-      const size_t p = (size_t)idx[0] + (size_t)nx * ((size_t)idx[1] + (size_t)ny * idx[2]);
-      const double2 v = ldc(r, p);
-      acc.x += wt * v.x;
-      acc.y += wt * v.y;
-    }
+    const double2 acc = sample_node<S>(g, r, j);
     const size_t off = m;
     x[j] = (T)(acc.x * inv);
     x[off + j] = (T)(acc.y * inv);
     if (!split_input && k_input && j == 0) x[2 * m] = (T)k;
+  }
+}
+
+// ---- branch network in two launches ------------------------------------------------
+// k_branch_first: the input layer's product, split over k: workgroup (i, c)
+// takes input entries [64 i, 64 i + 64) and columns [256 c, 256 c + 256), each
+// thread one column and half of the entries, its 32 weights all in flight.
+// They are issued first: the scale s = ||r|| / sqrt(n) (every workgroup sums the
+// norm's partials itself, in one order) and the workgroup's entries of the
+// branch input (sampled here, no array of them is formed) then cost no extra
+// memory latency.  k_branch_tail: one workgroup sums those products in order,
+// then runs the remaining layers (each thread a column and a quarter of k, BT_K
+// weights in flight, the next layer's first ones issued before this layer's sums
+// meet in LDS) and forms the coefficients c_j.  What bounds both is latency:
+// the 9.4 MB of weights (fp32, 8193-256x5) would take 2 us.  A launch per layer
+// and half layer, each thread walking its k with one load in flight and the
+// 256-wide layers on four workgroups, took 27.8 us per product and 16 launches
+// per correction (48^3 complex64: 179 -> 59 us, 16 of them
+// the synthesis).
+constexpr int BF_K = 64;        // input entries per workgroup
+constexpr int BT_K = 16;       // weights in flight per thread of the tail
+constexpr int BT_MAXL = 12;     // layers
+constexpr int BT_MAXW = 1024;   // outputs of a layer
+constexpr size_t BT_BYTES = (size_t)4 << 20;  // weights after the input layer: one CU reads them
+
+template <typename T>
+__global__ __launch_bounds__(512) void k_branch_first(SampleGrid g, const cplx_t<T>* __restrict__ r, size_t n,
+                                                      const double* __restrict__ npart, int nb, int B, int K, int N,
+                                                      int split_input, double kval, const T* __restrict__ W,
+                                                      double* __restrict__ part, double* __restrict__ sc) {
+  __shared__ double xs[2][BF_K], cmb[2][256], sh[16], s_inv;
+  const int t = threadIdx.x, half = t >> 8;
+  const int col = blockIdx.y * 256 + (t & 255), k0 = blockIdx.x * BF_K + half * (BF_K / 2);
+  T w[BF_K / 2];
+#pragma unroll
+  for (int u = 0; u < BF_K / 2; ++u) w[u] = (col < N && k0 + u < K) ? W[(size_t)(k0 + u) * N + col] : T(0);
+  double acc = 0.0;
+  if (t < 256)
+    for (int b0 = 0; b0 < nb; b0 += 4 * 256) {
+      double v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int b = b0 + t + 256 * q;
+        v[q] = b < nb ? npart[b] : 0.0;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc += v[q];
+    }
+  const size_t m = (size_t)g.m[0] * g.m[1] * g.m[2];
+  // entry k of input row b: split input Re (b = 0) and Im (b = 1) of node k;
+  // split output Re, then Im of the nodes, then the wave number
+  double xv = 0.0;
+  const int xb = t / BF_K, xk = blockIdx.x * BF_K + (t & (BF_K - 1));
+  bool scaled = true;
+  if (xb < B && xk < K) {
+    if (split_input) {
+      const double2 v = sample_node<T>(g, r, (size_t)xk);
+      xv = xb ? v.y : v.x;
+    } else if ((size_t)xk < 2 * m) {
+      const bool im = (size_t)xk >= m;
+      const double2 v = sample_node<T>(g, r, im ? xk - m : (size_t)xk);
+      xv = im ? v.y : v.x;
+    } else {
+      xv = kval;
+      scaled = false;
+    }
+  }
+  acc = block_sum(acc, sh);
+  if (t == 0) {
+    const double s = sqrt(acc / (double)n), inv = s > 0.0 ? 1.0 / s : 0.0;
+    s_inv = inv;
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+      sc[0] = s;
+      sc[1] = inv;
+    }
+  }
+  __syncthreads();
+  if (xb < B) xs[xb][t & (BF_K - 1)] = (double)(T)(scaled ? xv * s_inv : xv);
+  __syncthreads();
+  for (int b = 0; b < B; ++b) {
+    double a = 0.0;
+#pragma unroll
+    for (int u = 0; u < BF_K / 2; ++u) a += xs[b][half * (BF_K / 2) + u] * (double)w[u];
+    if (half) cmb[b][t & 255] = a;
+    __syncthreads();
+    if (!half && col < N) part[((size_t)blockIdx.x * B + b) * N + col] = a + cmb[b][t];
+  }
+}
+
+__device__ __forceinline__ double ld_weight(__amdgpu_buffer_rsrc_t r, int vo, int so, const double*) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, vo, so, 0));
+}
+__device__ __forceinline__ float ld_weight(__amdgpu_buffer_rsrc_t r, int vo, int so, const float*) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+}
+
+struct BranchTail {
+  int L, B, p, act, ns;           // layers; input rows; coefficients; activation; partials of the first product
+  int w[BT_MAXL + 1];             // widths
+  const void *W[BT_MAXL], *b[BT_MAXL];
+};
+
+template <typename T>
+__global__ __launch_bounds__(1024) void k_branch_tail(BranchTail a, const double* __restrict__ part,
+                                                      double* __restrict__ coef) {
+  __shared__ double x[2][2][BT_MAXW], red[4][2][256];
+  const int t = threadIdx.x, c = t & 255;
+  const int g = __builtin_amdgcn_readfirstlane(t >> 8);  // quarter of k; uniform in a wavefront
+  // the BT_K weights of the whole k chunk ch (entries BT_K ch and on) in
+  // column col (a column past the end reads 0, out of the buffer's range)
+  T wp[BT_K];
+  auto fetch = [&](int l, int ch, int col) {
+    const int K = a.w[l], N = a.w[l + 1], sz = (int)sizeof(T);
+    const __amdgpu_buffer_rsrc_t wr =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a.W[l]), 0, K * N * sz, 0x00020000);
+    const int vo = col < N ? (BT_K * ch * N + col) * sz : 0x7f000000;
+#pragma unroll
+    for (int u = 0; u < BT_K; ++u) wp[u] = ld_weight(wr, vo, u * N * sz, (const T*)nullptr);
+  };
+  // sums of a layer's output (row b, column col) meet in LDS: bias, activation
+  // (fp64 arithmetic, rounded once to the stored type)
+  auto finish = [&](int l, int dst, int col) {
+    const int N = a.w[l + 1];
+    __syncthreads();
+    if (g < a.B && col < N) {
+      double v = (red[0][g][c] + red[1][g][c]) + (red[2][g][c] + red[3][g][c]);
+      v += (double)((const T*)a.b[l])[col];
+      x[dst][g][col] = (double)(T)activate<double>(v, l + 1 < a.L ? a.act : ACT_NONE);
+    }
+    __syncthreads();
+  };
+  if (a.L > 1 && BT_K * (g + 1) <= a.w[1]) fetch(1, g, c);
+  {
+    const int N = a.w[1];
+    for (int n0 = 0; n0 < N; n0 += 256) {
+      const int col = n0 + c;
+      for (int b = 0; b < a.B; ++b) {
+        double acc = 0.0;
+        const double* q = part + (size_t)b * N + (col < N ? col : 0);
+        const size_t step = (size_t)a.B * N;
+#pragma unroll 1
+        for (int s0 = g; s0 < a.ns; s0 += 4 * 8) {
+          double v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) v[u] = s0 + 4 * u < a.ns ? q[(size_t)(s0 + 4 * u) * step] : 0.0;
+#pragma unroll
+          for (int u = 0; u < 8; ++u) acc += v[u];
+        }
+        red[g][b][c] = acc;
+      }
+      finish(0, 0, col);
+    }
+  }
+  int cur = 0;
+#pragma unroll 1
+  for (int l = 1; l < a.L; ++l) {
+    const int K = a.w[l], N = a.w[l + 1], nch = K / BT_K;
+#pragma unroll 1
+    for (int n0 = 0; n0 < N; n0 += 256) {
+      const int col = n0 + c;
+      double acc0 = 0.0, acc1 = 0.0;
+#pragma unroll 1
+      for (int ch = g; ch < nch; ch += 4) {
+        if (n0 > 0 || ch > g) fetch(l, ch, col);
+        const double* x0 = x[cur][0] + BT_K * ch;
+        const double* x1 = x[cur][1] + BT_K * ch;
+#pragma unroll
+        for (int u = 0; u < BT_K; ++u) acc0 += x0[u] * (double)wp[u];
+        if (a.B > 1)
+#pragma unroll
+          for (int u = 0; u < BT_K; ++u) acc1 += x1[u] * (double)wp[u];
+      }
+      if (K % BT_K && g == (nch & 3) && col < N) {  // the entries past the last whole chunk
+        const T* W = (const T*)a.W[l];
+        for (int k = BT_K * nch; k < K; ++k) {
+          const double wk = (double)W[(size_t)k * N + col];
+          acc0 += x[cur][0][k] * wk;
+          if (a.B > 1) acc1 += x[cur][1][k] * wk;
+        }
+      }
+      if (n0 + 256 >= N && l + 1 < a.L && BT_K * (g + 1) <= N) fetch(l + 1, g, c);
+      red[g][0][c] = acc0;
+      red[g][1][c] = acc1;
+      finish(l, 1 - cur, col);
+    }
+    cur = 1 - cur;
+  }
+  for (int j = t; j < a.p; j += blockDim.x) {
+    coef[2 * j] = x[cur][0][j];
+    coef[2 * j + 1] = a.B > 1 ? x[cur][1][j] : x[cur][0][a.p + j];
   }
 }
 
@@ -198,6 +396,30 @@ static bool same_grid(const don_s* net, const helm_op_s* op) {
   return true;
 }
 
+static SampleGrid sample_grid(const don_s* net, const helm_op_s* op) {
+  SampleGrid g;
+  g.dim = op->dim;
+  for (int a = 0; a < 3; ++a) {
+    g.n[a] = op->n[a];
+    g.m[a] = net->bgrid[a];
+  }
+  return g;
+}
+
+// k_branch_first + k_branch_tail: layer widths within the tail's LDS, its
+// weights few enough that one CU reads them faster than a launch or two per
+// layer would take (2 MB in fp64: about 15 us)
+static bool branch_fits(const don_s* net) {
+  const int L = (int)net->bw.size() - 1;
+  size_t bytes = 0;
+  if (L > BT_MAXL) return false;
+  for (int l = 0; l < L; ++l) {
+    if (net->bw[l + 1] > BT_MAXW) return false;
+    if (l > 0) bytes += (size_t)net->bw[l] * net->bw[l + 1] * (net->dt == HELM_C128 ? 8 : 4);
+  }
+  return bytes <= BT_BYTES;
+}
+
 template <typename T>
 static helm_status full_eval(don_s* net, helm_op_s* op, const void* r, double k, void* du, hipStream_t st,
                              bool input_only = false) {
@@ -215,6 +437,31 @@ static helm_status full_eval(don_s* net, helm_op_s* op, const void* r, double k,
   if ((s = op_part(op, (size_t)nb, &part))) return s;
   nrm2_part<T>(n, r, part, st);
   double* sv = op->red + 3072;  // [ss, s, 1/s]
+  if (!input_only && branch_fits(net)) {
+    const int B = net->head == DON_SPLIT_INPUT ? 2 : 1, K = net->bw[0], N = net->bw[1];
+    const int ns = (K + BF_K - 1) / BF_K;
+    if ((s = net->part.ensure((size_t)ns * B * N * sizeof(double))) ||
+        (s = net->coef.ensure(2 * (size_t)net->p * sizeof(double))))
+      return s;
+    hipLaunchKernelGGL((k_branch_first<T>), dim3(ns, (N + 255) / 256), dim3(512), 0, st, sample_grid(net, op),
+                       (const cplx_t<T>*)r, n, (const double*)part, nb, B, K, N, B == 2, k, (const T*)net->bW[0],
+                       (double*)net->part.ptr, sv + 1);
+    BranchTail a{};
+    a.L = (int)net->bw.size() - 1;
+    a.B = B;
+    a.p = net->p;
+    a.act = map_act(net->act);
+    a.ns = ns;
+    for (int l = 0; l <= a.L; ++l) a.w[l] = net->bw[l];
+    for (int l = 0; l < a.L; ++l) {
+      a.W[l] = net->bW[l];
+      a.b[l] = net->bB[l];
+    }
+    hipLaunchKernelGGL((k_branch_tail<T>), dim3(1), dim3(1024), 0, st, a, (const double*)net->part.ptr,
+                       (double*)net->coef.ptr);
+    skinny_apply<T, T>(n, net->p, (const T*)c.T.ptr, (const double*)net->coef.ptr, du, op->mask, sv + 1, 1, st);
+    return launch_check("deeponet full");
+  }
   reduce_cols(part, nb, 1, sv, st);
   hipLaunchKernelGGL(k_scale_of, dim3(1), dim3(64), 0, st, sv, (double)n, sv + 1);
   const double* sc = sv + 1;
@@ -237,9 +484,8 @@ static helm_status full_eval(don_s* net, helm_op_s* op, const void* r, double k,
     const size_t m = (size_t)net->bgrid[0] * net->bgrid[1] * net->bgrid[2];
     int g = (int)((m + 255) / 256);
     if (g > 8192) g = 8192;
-    hipLaunchKernelGGL((k_branch_in_sample<T, T>), dim3(g), dim3(256), 0, st, op->dim, op->n[0], op->n[1], op->n[2],
-                       net->bgrid[0], net->bgrid[1], net->bgrid[2], (const cplx_t<T>*)r, sc, split_in, net->k_input,
-                       k, x0);
+    hipLaunchKernelGGL((k_branch_in_sample<T, T>), dim3(g), dim3(256), 0, st, sample_grid(net, op),
+                       (const cplx_t<T>*)r, sc, split_in, net->k_input, k, x0);
   }
   if (input_only) {
     hipError_t e = hipMemcpyAsync(du, x0, (size_t)B * K0 * sizeof(T), hipMemcpyDeviceToDevice, st);
