@@ -51,6 +51,14 @@ void jacobi2_from_zero(const StencilGeom& g, const void* sc, const uint8_t* code
 template <typename S>
 void build_s(size_t n, const double* ksq, const double* alpha, void* sc, hipStream_t st);
 
+// ---- relax.hip --------------------------------------------------------------
+// `sweeps` relaxation sweeps (red-black, else damped Jacobi) in place on u,
+// ping-ponging through the field tmp: several Jacobi sweeps per launch where
+// that is faster, the same values bit for bit
+template <typename S>
+void relax_sweeps(const StencilGeom& g, const void* sc, const uint8_t* code, bool rbgs, double omega, int sweeps,
+                  const void* f, void* u, void* tmp, hipStream_t st);
+
 // ---- blas1.hip ------------------------------------------------------------
 int red_nblocks(size_t n);  // number of partials produced by the one-vector reductions
 // out[w] = sum_b part[b * width + w], b = 0..nparts-1 (fixed order), for w < width

@@ -48,16 +48,7 @@ static helm_status scratch_address(void** out) {
 template <typename S>
 static helm_status relax_static(helm_op_s* op, int kind, double omega, int sweeps, const void* f, void* u, void* tmp,
                                 hipStream_t st) {
-  void* a = u;
-  void* b = tmp;
-  for (int k = 0; k < sweeps; ++k) {
-    if (kind == HELM_RBGS) stencil_rbgs_fused<S>(op->geom, op->sc, op->code, f, a, b, omega, st);
-    else stencil_jacobi<S>(op->geom, op->sc, op->code, f, a, b, omega, st);
-    void* t = a;
-    a = b;
-    b = t;
-  }
-  if (a != u) copy_vec<S>(op->nn, a, u, st);
+  relax_sweeps<S>(op->geom, op->sc, op->code, kind == HELM_RBGS, omega, sweeps, f, u, tmp, st);
   return launch_check("helm_relax_noalloc");
 }
 

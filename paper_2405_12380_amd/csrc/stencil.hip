@@ -72,44 +72,6 @@ __global__ __launch_bounds__(512) void k_jacobi2z(StencilGeom g, const cplx_t<S>
 // so no other workgroup's output is ever read).  The per-node arithmetic is that
 // of the two colour passes of k_stencil<RBGS>, so the result is the same; HBM
 // sees one pass (uin, f, s and the code byte read, uout written).
-template <typename S>
-__device__ __forceinline__ double2 relax_upd(const StencilGeom& g, unsigned cd, double2 c, double2 a, double2 b,
-                                             double2 e, double2 h, double2 q, double2 w, double2 sp, double2 fp,
-                                             double omega, bool dim3) {
-  double2 ax;
-  if (cd & NB_SELF) {
-    ax = c;
-  } else {
-    a = sel0(cd & NB_XM, a);
-    b = sel0(cd & NB_XP, b);
-    e = sel0(cd & NB_YM, e);
-    h = sel0(cd & NB_YP, h);
-    double2 acc;
-    acc.x = ((c.x - a.x) + (c.x - b.x)) * g.ih2[0];
-    acc.y = ((c.y - a.y) + (c.y - b.y)) * g.ih2[0];
-    acc.x = acc.x + ((c.x - e.x) + (c.x - h.x)) * g.ih2[1];
-    acc.y = acc.y + ((c.y - e.y) + (c.y - h.y)) * g.ih2[1];
-    if (dim3) {
-      q = sel0(cd & NB_ZM, q);
-      w = sel0(cd & NB_ZP, w);
-      acc.x = acc.x + ((c.x - q.x) + (c.x - w.x)) * g.ih2[2];
-      acc.y = acc.y + ((c.y - q.y) + (c.y - w.y)) * g.ih2[2];
-    }
-    ax = csub(acc, cmul(sp, c));
-  }
-  const double2 r = csub(fp, ax);
-  const double2 d = (cd & NB_SELF) ? make_double2(1.0, 0.0) : make_double2(g.dsum - sp.x, -sp.y);
-  const double2 qq = ddiv(r, d);
-  return make_double2(c.x + omega * qq.x, c.y + omega * qq.y);
-}
-
-// a value rounded to the storage precision (what a pass through memory gives)
-template <typename S>
-__device__ __forceinline__ double2 rnd_store(double2 v) {
-  if (sizeof(S) == sizeof(float)) return make_double2((double)(float)v.x, (double)(float)v.y);
-  return v;
-}
-
 // the relaxation update at node (i, j, z) from the values of x alone (a red
 // node), rounded to the storage precision: the black updates read red values
 // as if the two colours were separate passes through memory
@@ -237,33 +199,12 @@ __global__ __launch_bounds__(512) void k_rbgs_fused(StencilGeom g, const cplx_t<
 // memory; the per-node arithmetic is relax_upd's.  Buffers must be under 2 GiB.
 constexpr int RB_TX = 64, RB_TY = 8, RB_LX = RB_TX + 4, RB_LY = RB_TY + 4, RB_PL = RB_LX * RB_LY, RB_NS = 6;
 constexpr int RB_RROW = (RB_TX + 2) / 2, RB_NRED = RB_RROW * (RB_TY + 2);  // red nodes of the tile and its rim (330)
-constexpr unsigned RB_OOB = 0x80000000u;  // byte offset past the end of every buffer the kernel is given
 // 384 threads: one red update per thread and step (330 on the tile and its
 // rim), one black update on the first 256 (the tile's 256 black nodes), the
 // staged plane three positions per thread
 constexpr int RB_NT = 384, RB_NB = RB_TX * RB_TY / 2;
 constexpr int RB_QP = (RB_PL + RB_NT - 1) / RB_NT, RB_RU = (RB_NRED + RB_NT - 1) / RB_NT;
 static_assert(RB_NB <= RB_NT && RB_RU == 1, "ring tile sizes");
-
-typedef unsigned int rb_u4 __attribute__((ext_vector_type(4)));
-typedef unsigned int rb_u2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rb_rsrc(const void* p, size_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off, const double2*) {
-  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
-__device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off, const float2*) {
-  const float2 v = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-  return make_double2((double)v.x, (double)v.y);
-}
-__device__ __forceinline__ void rb_st(__amdgpu_buffer_rsrc_t r, unsigned off, double2 v, double2*) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(rb_u4, v), r, off, 0, 0);
-}
-__device__ __forceinline__ void rb_st(__amdgpu_buffer_rsrc_t r, unsigned off, double2 v, float2*) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(rb_u2, make_float2((float)v.x, (float)v.y)), r, off, 0, 0);
-}
 
 // A node's data for one relaxation update: the aligned 32-bit word that holds
 // its code byte (a word, not the byte, so that a value carried into the next

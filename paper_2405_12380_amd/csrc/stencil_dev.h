@@ -271,4 +271,103 @@ __device__ __forceinline__ void jacobi2z_tile(const StencilGeom& g, unsigned lb,
   }
 }
 
+// One relaxation update of eq. 2 at a node: c its value, a, b, e, h, q, w its
+// x-, x+, y-, y+, z-, z+ neighbours (absent ones by the code cd), sp and fp its
+// s and f.
+template <typename S>
+__device__ __forceinline__ double2 relax_upd(const StencilGeom& g, unsigned cd, double2 c, double2 a, double2 b,
+                                             double2 e, double2 h, double2 q, double2 w, double2 sp, double2 fp,
+                                             double omega, bool dim3) {
+  double2 ax;
+  if (cd & NB_SELF) {
+    ax = c;
+  } else {
+    a = sel0(cd & NB_XM, a);
+    b = sel0(cd & NB_XP, b);
+    e = sel0(cd & NB_YM, e);
+    h = sel0(cd & NB_YP, h);
+    double2 acc;
+    acc.x = ((c.x - a.x) + (c.x - b.x)) * g.ih2[0];
+    acc.y = ((c.y - a.y) + (c.y - b.y)) * g.ih2[0];
+    acc.x = acc.x + ((c.x - e.x) + (c.x - h.x)) * g.ih2[1];
+    acc.y = acc.y + ((c.y - e.y) + (c.y - h.y)) * g.ih2[1];
+    if (dim3) {
+      q = sel0(cd & NB_ZM, q);
+      w = sel0(cd & NB_ZP, w);
+      acc.x = acc.x + ((c.x - q.x) + (c.x - w.x)) * g.ih2[2];
+      acc.y = acc.y + ((c.y - q.y) + (c.y - w.y)) * g.ih2[2];
+    }
+    ax = csub(acc, cmul(sp, c));
+  }
+  const double2 r = csub(fp, ax);
+  const double2 d = (cd & NB_SELF) ? make_double2(1.0, 0.0) : make_double2(g.dsum - sp.x, -sp.y);
+  const double2 qq = ddiv(r, d);
+  return make_double2(c.x + omega * qq.x, c.y + omega * qq.y);
+}
+
+// (A x) at a node of a 2D grid, the arithmetic of relax_upd
+template <typename S>
+__device__ __forceinline__ double2 stencil_row2(const StencilGeom& g, unsigned cd, double2 c, double2 a, double2 b,
+                                                double2 e, double2 h, double2 sp) {
+  if (cd & NB_SELF) return c;
+  a = sel0(cd & NB_XM, a);
+  b = sel0(cd & NB_XP, b);
+  e = sel0(cd & NB_YM, e);
+  h = sel0(cd & NB_YP, h);
+  double2 acc;
+  acc.x = ((c.x - a.x) + (c.x - b.x)) * g.ih2[0];
+  acc.y = ((c.y - a.y) + (c.y - b.y)) * g.ih2[0];
+  acc.x = acc.x + ((c.x - e.x) + (c.x - h.x)) * g.ih2[1];
+  acc.y = acc.y + ((c.y - e.y) + (c.y - h.y)) * g.ih2[1];
+  return csub(acc, cmul(sp, c));
+}
+
+// a value rounded to the storage precision (what a pass through memory gives)
+template <typename S>
+__device__ __forceinline__ double2 rnd_store(double2 v) {
+  if (sizeof(S) == sizeof(float)) return make_double2((double)(float)v.x, (double)(float)v.y);
+  return v;
+}
+
+// Buffer addressing of a field (32-bit byte offsets: fields under 2 GiB): an
+// offset past the end (RB_OOB) reads 0 and stores nothing.
+constexpr unsigned RB_OOB = 0x80000000u;  // byte offset past the end of every buffer the kernel is given
+typedef unsigned int rb_u4 __attribute__((ext_vector_type(4)));
+typedef unsigned int rb_u2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rb_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off, const double2*) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+__device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off, const float2*) {
+  const float2 v = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+  return make_double2((double)v.x, (double)v.y);
+}
+// the same with a uniform part `so` of the offset (so < the buffer's size)
+__device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned so, const double2*) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, so, 0));
+}
+__device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned so, const float2*) {
+  const float2 v = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, so, 0));
+  return make_double2((double)v.x, (double)v.y);
+}
+__device__ __forceinline__ void rb_st(__amdgpu_buffer_rsrc_t r, unsigned off, double2 v, double2*) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(rb_u4, v), r, off, 0, 0);
+}
+__device__ __forceinline__ void rb_st(__amdgpu_buffer_rsrc_t r, unsigned off, double2 v, float2*) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(rb_u2, make_float2((float)v.x, (float)v.y)), r, off, 0, 0);
+}
+
+// streaming (non-temporal) stores
+constexpr int RB_NT_AUX = 2;
+__device__ __forceinline__ void rb_st(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned so, double2 v, double2*) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(rb_u4, v), r, off, so, RB_NT_AUX);
+}
+__device__ __forceinline__ void rb_st(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned so, double2 v, float2*) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(rb_u2, make_float2((float)v.x, (float)v.y)), r, off, so,
+                                        RB_NT_AUX);
+}
+
 }  // namespace helm
