@@ -10,17 +10,14 @@
 // Gauss-Jordan with partial pivoting.
 //
 // Correction z += X (X^T A X)^{-1} X^T r1 (HBM-bound skinny products):
-//   k_qt_part   per-block partials of Q^T r1: lanes own columns {l, l+64},
-//               the grid's wavefronts sweep Q in four-row groups, one
-//               coalesced 2 x 512 B row read per row;
-//   k_ainv      c = A_c^{-1} y, one workgroup per row of A_c^{-1};
-//   k_skinny    y_i = sum_j Q_ij c_j: lanes own columns, four rows per step,
-//               reduced with an 11-shuffle butterfly that leaves row rho's
-//               (re, im) in lane 16 rho.
+//   k_qt_part      per-block partials of Q^T r1;
+//   k_reduce_ainv  their sum y and c = A_c^{-1} y;
+//   k_skinny       z_i += sum_j Q_ij c_j.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -33,205 +30,88 @@
 
 namespace helm {
 
-static constexpr int QT_MAXB = 512;
-
-int qt_nblocks(size_t n) {
-  size_t nb = (n + 511) / 512;
-  if (nb > QT_MAXB) nb = QT_MAXB;
-  if (nb < 1) nb = 1;
-  return (int)nb;
+static constexpr size_t QT_MAXB = 256;
+// lanes that read one row of r columns of esz-byte values, 16 bytes each
+static int qt_lanes(int r, size_t esz) {
+  const int need = (int)((r * esz + 15) / 16);
+  return need <= 8 ? 8 : need <= 16 ? 16 : need <= 32 ? 32 : 64;
+}
+// How a basis is loaded: through the caches up to 192 MB, where most of it is
+// still in the 256 MB memory-side cache at the next pass (56 x 48 x 52, r = 96,
+// 107 MB: one inversion step 4870 us, against 5170 streaming); streaming
+// beyond, where it would only push the Krylov vectors out (64^3, r = 128, 268 MB:
+// a 60-step GMRES solve 14020 us, against 14290 cached).  Rows that are not
+// 16-byte aligned go value by value.
+static int q_load(size_t n, int r, size_t esz) {
+  if (r * esz % 16) return LD_VALUES;
+  return n * r * esz <= ((size_t)192 << 20) ? LD_CACHED : LD_STREAM;
+}
+// workgroups of the restriction: at most one to a CU (the partials they write
+// are read again by every workgroup of k_reduce_ainv), fewer where a
+// wavefront would have no rows
+static int qt_nblocks(size_t n, int r, size_t esz) {
+  const size_t rows = (size_t)QT_WAVES * QT_U * (64 / qt_lanes(r, esz));
+  const size_t nb = (n + rows - 1) / rows;
+  return (int)(nb < QT_MAXB ? nb : QT_MAXB);
 }
 
-// the fp32-basis restriction reads half the bytes per row and runs twice the
-// workgroups to keep as many bytes in flight
-static constexpr int QT32_MAXB = 1024;
-int qt_nblocks32(size_t n) {
-  size_t nb = (n + 255) / 256;
-  if (nb > QT32_MAXB) nb = QT32_MAXB;
-  if (nb < 1) nb = 1;
-  return (int)nb;
+template <typename T, typename S, int LPR, int LD>
+__global__ __launch_bounds__(64 * QT_WAVES) void k_qt_part(size_t n, int r, const T* __restrict__ Q,
+                                                           const cplx_t<S>* __restrict__ x,
+                                                           double* __restrict__ part) {
+  qt_sweep<T, S, LPR, LD>(n, r, Q, x, (blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6,
+                      ((size_t)gridDim.x * blockDim.x) >> 6, part + (size_t)blockIdx.x * 2 * r);
 }
 
-// part[b][2j + {0,1}] = sum over the rows of block b of Q_ij x_i (complex x,
-// real Q, j < r <= 128).  Rows go in groups of four; wavefront g of the W in
-// the grid takes groups g, g + W, g + 2W, ..., so at any moment the whole grid
-// reads one contiguous stretch of Q (DRAM pages stay open; this sweep is ~8%
-// faster than giving each block a contiguous range).  The row-to-block
-// assignment depends only on n, so the partials are reproducible.
-template <typename T, typename S>
-__global__ __launch_bounds__(256) void k_qt_part(size_t n, int r, const T* __restrict__ Q,
-                                                 const cplx_t<S>* __restrict__ x, double* __restrict__ part) {
-  __shared__ double sh[4][256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int c0 = lane, c1 = lane + 64;
-  const bool u0 = c0 < r, u1 = c1 < r;
-  const size_t W = ((size_t)gridDim.x * blockDim.x) >> 6, ng = (n + 3) / 4;
-  double a0r = 0, a0i = 0, a1r = 0, a1i = 0;
-  for (size_t g = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6; g < ng; g += W) {
-    double q0[4], q1[4];
-    double2 xv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const size_t ii = 4 * g + u;
-      const bool in = ii < n;
-      xv[u] = in ? ldc(x, ii) : czero();
-      q0[u] = in && u0 ? ldq(Q, ii * r + c0) : 0.0;
-      q1[u] = in && u1 ? ldq(Q, ii * r + c1) : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a0r += q0[u] * xv[u].x;
-      a0i += q0[u] * xv[u].y;
-      a1r += q1[u] * xv[u].x;
-      a1i += q1[u] * xv[u].y;
-    }
-  }
-  sh[wave][2 * c0] = a0r;
-  sh[wave][2 * c0 + 1] = a0i;
-  sh[wave][2 * c1] = a1r;
-  sh[wave][2 * c1 + 1] = a1i;
-  __syncthreads();
-  for (int e = threadIdx.x; e < 2 * r; e += blockDim.x)
-    part[(size_t)blockIdx.x * 2 * r + e] = (sh[0][e] + sh[1][e]) + (sh[2][e] + sh[3][e]);
-}
-
-// fp32 basis: each half-wavefront takes one row, lane m of it the four
-// columns 4m .. 4m + 3 (one 16-byte load; a wavefront reads two 512 B rows per
-// instruction); groups of four row pairs in the same grid sweep.  Rows whose
-// length r is not a multiple of 4 are read one float at a time.
-template <typename S>
-__global__ __launch_bounds__(256) void k_qt_part32(size_t n, int r, const float* __restrict__ Q,
-                                                   const cplx_t<S>* __restrict__ x, double* __restrict__ part) {
-  constexpr int U = 4;
-  __shared__ double sh[4][2][256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int h = lane >> 5, m = lane & 31;
-  const bool v4 = (r & 3) == 0;
-  const size_t W = ((size_t)gridDim.x * blockDim.x) >> 6, ng = (n + 2 * U - 1) / (2 * U);
-  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (size_t g = (blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6; g < ng; g += W) {
-    float4 q[U];
-    double2 xv[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t ii = 2 * U * g + 2 * u + h;
-      const bool in = ii < n;
-      xv[u] = in ? ldc(x, ii) : czero();
-      if (in && v4 && 4 * m < r) {
-        q[u] = *reinterpret_cast<const float4*>(Q + ii * r + 4 * m);
-      } else {
-        const float* row = Q + ii * r;
-        const int c = 4 * m;
-        q[u] = make_float4(in && c < r ? row[c] : 0.f, in && c + 1 < r ? row[c + 1] : 0.f,
-                           in && c + 2 < r ? row[c + 2] : 0.f, in && c + 3 < r ? row[c + 3] : 0.f);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      acc[0] += (double)q[u].x * xv[u].x;
-      acc[1] += (double)q[u].x * xv[u].y;
-      acc[2] += (double)q[u].y * xv[u].x;
-      acc[3] += (double)q[u].y * xv[u].y;
-      acc[4] += (double)q[u].z * xv[u].x;
-      acc[5] += (double)q[u].z * xv[u].y;
-      acc[6] += (double)q[u].w * xv[u].x;
-      acc[7] += (double)q[u].w * xv[u].y;
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < 8; ++k) sh[wave][h][8 * m + k] = acc[k];  // = 2 column + (re, im)
-  __syncthreads();
-  for (int e = threadIdx.x; e < 2 * r; e += blockDim.x) {
-    double v = 0.0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) v += sh[w][0][e] + sh[w][1][e];
-    part[(size_t)blockIdx.x * 2 * r + e] = v;
-  }
-}
-
-// c = Ainv y: block j computes row j (r x r complex, row-major)
-__global__ __launch_bounds__(64) void k_ainv(int r, const double* __restrict__ Ainv, const double* __restrict__ y,
-                                             double* __restrict__ c) {
-  const int j = blockIdx.x, l = threadIdx.x;
+// y = the sum of the restriction's nb partials (in a fixed order), c = Ainv y
+// (r x r complex, row-major).  Workgroup b forms y for itself and then rows 16 b
+// .. 16 b + 15 of c, a wavefront each, with the row of Ainv loaded before the
+// partials.  What bounds it is the 2 r nb doubles one CU reads: 8.8 us at
+// r = 128 and 256 partials (two launches, the sums and the product, took 4.8 and
+// 4.6 us and a gap), 4.5 us on small grids (two launches: 6.4 to 9).
+__global__ __launch_bounds__(1024) void k_reduce_ainv(int r, int nb, const double* __restrict__ part,
+                                                      const double* __restrict__ Ainv, double* __restrict__ c) {
+  __shared__ double2 sh[8][128], y[128];
+  const int t = threadIdx.x, lane = t & 63, j = blockIdx.x * 16 + (t >> 6);
+  const double2* A = reinterpret_cast<const double2*>(Ainv) + (size_t)(j < r ? j : 0) * r;
+  const double2 a0 = lane < r ? A[lane] : czero(), a1 = lane + 64 < r ? A[lane + 64] : czero();
+  const int e = t & 127, s = t >> 7;
+  const double2* p2 = reinterpret_cast<const double2*>(part) + e;
   double2 acc = czero();
-  for (int k0 = 0; k0 < r; k0 += 128) {  // both halves' loads in flight at once
-    double2 a[2], b[2];
+  if (e < r)
+    for (int b0 = s; b0 < nb; b0 += 8 * 16) {
+      double2 v[16];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int k = k0 + l + 64 * q;
-      const size_t o = 2 * ((size_t)j * r + k);
-      a[q] = k < r ? make_double2(Ainv[o], Ainv[o + 1]) : czero();
-      b[q] = k < r ? make_double2(y[2 * k], y[2 * k + 1]) : czero();
+      for (int u = 0; u < 16; ++u) v[u] = b0 + 8 * u < nb ? p2[(size_t)(b0 + 8 * u) * r] : czero();
+#pragma unroll
+      for (int u = 0; u < 16; ++u) acc = cadd(acc, v[u]);
     }
+  sh[s][e] = acc;
+  __syncthreads();
+  if (t < 128) {
+    double2 v = sh[0][t];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) acc = cadd(acc, cmul(a[q], b[q]));
+    for (int k = 1; k < 8; ++k) v = cadd(v, sh[k][t]);
+    y[t] = v;
   }
-  acc.x = wave_sum(acc.x);
-  acc.y = wave_sum(acc.y);
-  if (l == 0) {
-    c[2 * j] = acc.x;
-    c[2 * j + 1] = acc.y;
+  __syncthreads();
+  double2 v = czero();
+  if (lane < r) v = cmul(a0, y[lane]);
+  if (lane + 64 < r) v = cadd(v, cmul(a1, y[lane + 64]));
+  v.x = wave_sum(v.x);
+  v.y = wave_sum(v.y);
+  if (lane == 0 && j < r) {
+    c[2 * j] = v.x;
+    c[2 * j + 1] = v.y;
   }
 }
 
-template <typename T, typename S, int MODE>
+template <typename T, typename S, int MODE, int LPR, int LD>
 __global__ __launch_bounds__(256) void k_skinny(size_t n, int r, const T* __restrict__ Q, const double* __restrict__ c,
                                                 cplx_t<S>* __restrict__ z, const uint8_t* __restrict__ mask,
                                                 const double* __restrict__ scal) {
-  skinny_rows<T, S, MODE>(n, r, Q, c, z, mask, scal, (blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6,
-                          ((size_t)gridDim.x * blockDim.x) >> 6);
-}
-
-// fp32 basis version of k_skinny: one row per thread, the row read in 16-byte
-// pieces (one float at a time when r is not a multiple of 4), c staged in LDS;
-// no cross-lane reduction, so the half-size rows do not leave the shuffles
-// dominant.  Same two modes as k_skinny.
-template <typename S, int MODE>
-__global__ __launch_bounds__(256) void k_skinny32(size_t n, int r, const float* __restrict__ Q,
-                                                  const double* __restrict__ c, cplx_t<S>* __restrict__ z,
-                                                  const uint8_t* __restrict__ mask, const double* __restrict__ scal) {
-  __shared__ double2 cs[128];
-  const int t = threadIdx.x;
-  if (t < 128) cs[t] = t < r ? make_double2(c[2 * t], c[2 * t + 1]) : czero();
-  __syncthreads();
-  double sc = 1.0;
-  if (MODE == SK_SYNTH) sc = scal[0];
-  const bool v4 = (r & 3) == 0;
-  const int nq = (r + 3) / 4;  // 16-byte pieces per row (at most 32)
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + t; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const float* row = Q + i * r;
-    double yr = 0.0, yi = 0.0;
-#pragma unroll 1
-    for (int j0 = 0; j0 < nq; j0 += 8) {
-      float4 q[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int cq = 4 * (j0 + u);
-        if (j0 + u < nq && v4) {
-          q[u] = *reinterpret_cast<const float4*>(row + cq);
-        } else {
-          q[u] = make_float4(cq < r ? row[cq] : 0.f, cq + 1 < r ? row[cq + 1] : 0.f, cq + 2 < r ? row[cq + 2] : 0.f,
-                             cq + 3 < r ? row[cq + 3] : 0.f);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int cq = 4 * (j0 + u);  // <= 124: cs[] beyond r holds zeros
-        const double2 c0 = cs[cq], c1 = cs[cq + 1], c2 = cs[cq + 2], c3 = cs[cq + 3];
-        yr += (double)q[u].x * c0.x;
-        yi += (double)q[u].x * c0.y;
-        yr += (double)q[u].y * c1.x;
-        yi += (double)q[u].y * c1.y;
-        yr += (double)q[u].z * c2.x;
-        yi += (double)q[u].z * c2.y;
-        yr += (double)q[u].w * c3.x;
-        yi += (double)q[u].w * c3.y;
-      }
-    }
-    const double2 y = make_double2(yr, yi);
-    if (MODE == SK_ADD) stc(z, i, cadd(ldc(z, i), y));
-    else stc(z, i, mask[i] ? czero() : cscale(y, sc));
-  }
+  skinny_sweep<T, S, MODE, LPR, LD>(n, r, Q, c, z, mask, scal, (blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6,
+                                ((size_t)gridDim.x * blockDim.x) >> 6);
 }
 
 // B = (L - diag(Re s)) Q on real columns (n x r, row-major); masked rows -> 0.
@@ -358,15 +238,43 @@ static unsigned ew_grid(size_t total) {
 }
 
 // ---- launchers used by other units ------------------------------------------------
+// the kernels' instances by lanes per row and by whether rows are 16-byte aligned
+template <typename T, typename S, int LD>
+static void qt_launch(int lpr, int nb, size_t n, int r, const T* Q, const cplx_t<S>* x, double* part, hipStream_t st) {
+  const dim3 grid(nb), block(64 * QT_WAVES);
+  switch (lpr) {
+    case 8: hipLaunchKernelGGL((k_qt_part<T, S, 8, LD>), grid, block, 0, st, n, r, Q, x, part); break;
+    case 16: hipLaunchKernelGGL((k_qt_part<T, S, 16, LD>), grid, block, 0, st, n, r, Q, x, part); break;
+    case 32: hipLaunchKernelGGL((k_qt_part<T, S, 32, LD>), grid, block, 0, st, n, r, Q, x, part); break;
+    default: hipLaunchKernelGGL((k_qt_part<T, S, 64, LD>), grid, block, 0, st, n, r, Q, x, part);
+  }
+}
+template <typename T, typename S, int MODE, int LD>
+static void skinny_launch(int lpr, size_t n, int r, const T* Q, const double* c, cplx_t<S>* z, const uint8_t* mask,
+                          const double* scal, hipStream_t st) {
+  const size_t rows = 4 * 4 * (64 / lpr);  // of a workgroup's four wavefronts
+  size_t nb = (n + rows - 1) / rows;
+  if (nb > 1024) nb = 1024;
+  const dim3 grid((unsigned)nb), block(256);
+  switch (lpr) {
+    case 8: hipLaunchKernelGGL((k_skinny<T, S, MODE, 8, LD>), grid, block, 0, st, n, r, Q, c, z, mask, scal); break;
+    case 16: hipLaunchKernelGGL((k_skinny<T, S, MODE, 16, LD>), grid, block, 0, st, n, r, Q, c, z, mask, scal); break;
+    case 32: hipLaunchKernelGGL((k_skinny<T, S, MODE, 32, LD>), grid, block, 0, st, n, r, Q, c, z, mask, scal); break;
+    default: hipLaunchKernelGGL((k_skinny<T, S, MODE, 64, LD>), grid, block, 0, st, n, r, Q, c, z, mask, scal);
+  }
+}
+
 // returns the number of partial rows written
 template <typename T, typename S>
 int qt_partials(size_t n, int r, const T* Q, const void* x, double* part, hipStream_t st) {
-  const int nb = sizeof(T) == sizeof(float) ? qt_nblocks32(n) : qt_nblocks(n);
+  const int nb = qt_nblocks(n, r, sizeof(T)), lpr = qt_lanes(r, sizeof(T));
+  const cplx_t<S>* xc = (const cplx_t<S>*)x;
   kprof_begin(KP_QT, st);
-  if (sizeof(T) == sizeof(float))
-    hipLaunchKernelGGL((k_qt_part32<S>), dim3(nb), dim3(256), 0, st, n, r, (const float*)Q, (const cplx_t<S>*)x, part);
-  else
-    hipLaunchKernelGGL((k_qt_part<T, S>), dim3(nb), dim3(256), 0, st, n, r, Q, (const cplx_t<S>*)x, part);
+  switch (q_load(n, r, sizeof(T))) {
+    case LD_VALUES: qt_launch<T, S, LD_VALUES>(lpr, nb, n, r, Q, xc, part, st); break;
+    case LD_CACHED: qt_launch<T, S, LD_CACHED>(lpr, nb, n, r, Q, xc, part, st); break;
+    default: qt_launch<T, S, LD_STREAM>(lpr, nb, n, r, Q, xc, part, st);
+  }
   kprof_end(KP_QT, (double)n * (sizeof(T) * r + 2 * sizeof(S)), st);
   return nb;
 }
@@ -374,28 +282,18 @@ int qt_partials(size_t n, int r, const T* Q, const void* x, double* part, hipStr
 template <typename T, typename S>
 void skinny_apply(size_t n, int r, const T* Q, const double* c, void* z, const uint8_t* mask, const double* scal,
                   int synth, hipStream_t st) {
-  size_t waves = (n + 3) / 4;
-  size_t nb = (waves + 3) / 4;
-  if (nb > 4096) nb = 4096;
-  if (nb < 1) nb = 1;
   kprof_begin(KP_SKINNY, st);
-  if (sizeof(T) == sizeof(float)) {
-    const float* Qf = (const float*)Q;
-    nb = (n + 255) / 256;  // one row per thread, grid-strided
-    if (nb > 1024) nb = 1024;
-    if (synth)
-      hipLaunchKernelGGL((k_skinny32<S, SK_SYNTH>), dim3((unsigned)nb), dim3(256), 0, st, n, r, Qf, c, (cplx_t<S>*)z,
-                         mask, scal);
-    else
-      hipLaunchKernelGGL((k_skinny32<S, SK_ADD>), dim3((unsigned)nb), dim3(256), 0, st, n, r, Qf, c, (cplx_t<S>*)z,
-                         mask, scal);
-  } else if (synth) {
-    hipLaunchKernelGGL((k_skinny<T, S, SK_SYNTH>), dim3((unsigned)nb), dim3(256), 0, st, n, r, Q, c, (cplx_t<S>*)z,
-                       mask, scal);
-  } else {
-    hipLaunchKernelGGL((k_skinny<T, S, SK_ADD>), dim3((unsigned)nb), dim3(256), 0, st, n, r, Q, c, (cplx_t<S>*)z, mask,
-                       scal);
-  }
+  const int lpr = qt_lanes(r, sizeof(T));
+  const int ld = q_load(n, r, sizeof(T));
+  cplx_t<S>* zc = (cplx_t<S>*)z;
+  auto launch = [&](auto mode) {
+    constexpr int MODE = decltype(mode)::value;
+    if (ld == LD_VALUES) skinny_launch<T, S, MODE, LD_VALUES>(lpr, n, r, Q, c, zc, mask, scal, st);
+    else if (ld == LD_CACHED) skinny_launch<T, S, MODE, LD_CACHED>(lpr, n, r, Q, c, zc, mask, scal, st);
+    else skinny_launch<T, S, MODE, LD_STREAM>(lpr, n, r, Q, c, zc, mask, scal, st);
+  };
+  if (synth) launch(std::integral_constant<int, SK_SYNTH>{});
+  else launch(std::integral_constant<int, SK_ADD>{});
   // Q once; z read and written (ADD) or du written and the mask read (SYNTH)
   kprof_end(KP_SKINNY, (double)n * (sizeof(T) * r + (synth ? 2 * sizeof(S) + 1 : 4 * sizeof(S))), st);
 }
@@ -543,7 +441,7 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
   if ((s = c.Q.ensure(n * (size_t)r * (c.q_f32 ? sizeof(float) : sizeof(double)))) ||
       (s = c.W1.ensure(n * (size_t)r * sizeof(double))) || (s = c.Ac.ensure(2 * sizeof(double) * r * r)) ||
       (s = c.Ainv.ensure(2 * sizeof(double) * r * r)) ||
-      (s = c.qpart.ensure(sizeof(double) * 2 * (size_t)r * std::max(qt_nblocks(n), qt_nblocks32(n)))))
+      (s = c.qpart.ensure(sizeof(double) * 2 * (size_t)r * qt_nblocks(n, r, c.q_f32 ? sizeof(float) : sizeof(double)))))
     return s;
   // the Galerkin matrix X^T A X = X^T B - i X^T diag(Im s) X of an n x r basis
   // X into out (complex r x r); B = (L - diag(Re s)) X and then Im s go
@@ -662,12 +560,11 @@ helm_status coarse_correct(helm_op_s* op, const void* r1, void* z, hipStream_t s
   if (r == 0) return HELM_OK;
   const size_t n = op->nn;
   double* part = (double*)c.qpart.ptr;
-  double* y = op->red + 1024;
   double* cc = op->red + 2048;
   const int nb = c.q_f32 ? qt_partials<float, S>(n, r, (const float*)c.Q.ptr, r1, part, st)
                          : qt_partials<double, S>(n, r, (const double*)c.Q.ptr, r1, part, st);
-  reduce_cols(part, nb, 2 * r, y, st);
-  hipLaunchKernelGGL(k_ainv, dim3(r), dim3(64), 0, st, r, (const double*)c.Ainv.ptr, y, cc);
+  hipLaunchKernelGGL(k_reduce_ainv, dim3((r + 15) / 16), dim3(1024), 0, st, r, nb, (const double*)part,
+                     (const double*)c.Ainv.ptr, cc);
   if (c.q_f32) skinny_apply<float, S>(n, r, (const float*)c.Q.ptr, cc, z, op->mask, nullptr, 0, st);
   else skinny_apply<double, S>(n, r, (const double*)c.Q.ptr, cc, z, op->mask, nullptr, 0, st);
   return launch_check("coarse correction");
