@@ -9,17 +9,20 @@
 //   back:    dT = dUt^T Bc, dBc = dUt T, then per layer dW = H^T dZ, db = colsum dZ,
 //            dZ_below = (dZ W^T) * (1 - H^2)
 //   Adam on the flat fp32 parameters; bf16 copies feed the next step's GEMMs.
-// Every matrix product runs in one bf16 GEMM kernel, C = A B^T with both
+// The trunk's rows are the P points, so its products are tall: its forward pass
+// is one launch (k_mlp_fwd), its backward pass one launch per layer
+// (k_bwd_layer), the output product, the loss and their gradients two (k_out),
+// each reading every activation once, row-major.  The branch's products, and
+// any product of the general form, run in one bf16 GEMM kernel, C = A B^T with both
 // operands k-contiguous (v_mfma_f32_16x16x32_bf16, 128 x 128 tile per
 // 256-thread workgroup, 64-deep k steps through LDS with the next step's
 // operands prefetched into registers), with fused epilogues (bias + tanh, bias,
-// tanh derivative, fp32) or split-k partials reduced in a fixed order.  So that
-// every product is of that form, the epilogues also write a transposed copy of
-// each activation and each gradient (the backward products reduce over the
-// points, which must then be contiguous), and Adam refreshes both W and W^T in
-// bf16.  The branch MLP (forward and backward) runs on a second stream beside
-// the trunk, and the trunk's bias row sums on a third beside its weight
-// products.  Steps are captured as HIP graphs (one step, and eight steps per
+// tanh derivative, fp32) or split-k partials reduced in a fixed order; for it
+// the branch's epilogues also write a transposed copy of each activation and
+// gradient, and Adam refreshes both W and W^T in bf16.  The branch MLP (forward
+// and backward) runs on a second stream beside the trunk.  fp32 sums keep one
+// order whichever kernel forms them (the row ranges of splits_for, added in
+// turn).  Steps are captured as HIP graphs (one step, and eight steps per
 // launch) and replayed; the sample indices and the step counter live on the
 // device.
 #include <hip/hip_runtime.h>
@@ -275,7 +278,7 @@ struct FwdArgs {
   const __bf16* wt[FW_MAXL];    // W^T, N x Kp, k-contiguous
   const float* bias[FW_MAXL];
   __bf16* h[FW_MAXL];   // M x N
-  __bf16* hT[FW_MAXL];  // N x M
+  __bf16* hT[FW_MAXL];  // N x M, or NULL where nobody reads it
 };
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp_fwd(FwdArgs a) {
@@ -352,7 +355,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       if (m0 + r < a.M)  // read again only in the backward pass: streaming stores
         __builtin_nontemporal_store(*(const bf8*)(act + asw(r, cq)), (bf8*)(a.h[li] + (long)(m0 + r) * N + cq));
     }
-    for (int c = t; c < N * (TM / 8); c += 256) {
+    if (a.hT[li]) for (int c = t; c < N * (TM / 8); c += 256) {
       const int col = c / (TM / 8), rq = (c % (TM / 8)) * 8;
       bf8 v;
 #pragma unroll
@@ -360,6 +363,217 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       if (m0 + rq + 8 <= a.M) __builtin_nontemporal_store(v, (bf8*)(a.hT[li] + (long)col * a.M + m0 + rq));
     }
   }
+}
+
+// ---- one trunk layer's backward pass in one launch ------------------------------------
+// From dZ (M x N) of a layer and its input H (M x K): dZ_below = (dZ W^T) * (1 -
+// H^2), and partials of dW = H^T dZ and of db = the column sums of dZ.
+// A workgroup of 256 threads takes 64 input columns and a range of 64-row blocks:
+// a block of dZ and H is staged in LDS once for
+// all three results (the next one in registers meanwhile), and its dW stays
+// in the accumulators until the last block.  So every activation and gradient
+// is read once and row-major; the operands that run along the rows are read
+// from LDS transposed (ds_read_b64_tr_b16: the 16 lanes of a group read four
+// rows of 16 columns and receive a column of four each).  Bound by HBM: dZ, H in
+// and dZ_below out are 170 MB at M = 110592, 256 wide.  dZ_below is k_gemm_nt's
+// value bit for bit (same operands, k order and epilogue); db is summed in fp64.
+// One product each for dZ_below and dW, the latter over transposed copies that
+// every kernel wrote beside the plain ones, and a pass of row sums took 115 us for
+// a 256-wide layer; this takes 55 (3.1 TB/s).  The wavefront's part of W stays in
+// registers over the blocks (loaded from L2 in every step: 108 us), and workgroups
+// of four wavefronts go two to a CU so that one's barriers overlap the other's
+// products (one of eight: 70 us).
+constexpr int BW_R = 64, BW_C = 64;                                  // rows per block, input columns per workgroup
+constexpr int BW_T = 256;                                             // threads
+constexpr int BW_LN = 256 + 16, BW_LH = BW_C + 16, BW_LO = BW_C + 8;  // LDS row strides (bf16): 8 (4) banks a row
+struct BwdArgs {
+  int M, K, chunk;           // rows, input columns, row blocks per workgroup
+  const __bf16 *dZ, *H, *W;  // M x N; M x K; K x N
+  __bf16* dZb;               // M x K, or NULL (the first layer)
+  float* part;               // row ranges x K x N
+  double* dbpart;            // row ranges x N
+};
+
+typedef short s4 __attribute__((ext_vector_type(4)));
+// eight consecutive rows r .. r + 7 of LDS column c of a 16-lane group, for lane
+// l of the group column c0 + l % 16: the k-contiguous MFMA operand of a
+// row-major tile (ld: its row stride)
+__device__ __forceinline__ bf8 ld_tr(const __bf16* tile, int ld, int r, int c0, int l) {
+  typedef __attribute__((address_space(3))) s4 lds_s4;
+  const __bf16* p = tile + (r + (l >> 2)) * ld + c0 + 4 * (l & 3);
+  const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p));
+  const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p + 4 * ld));
+  typedef short s8 __attribute__((ext_vector_type(8)));
+  return __builtin_bit_cast(bf8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int N>
+__global__ __launch_bounds__(BW_T, 2) void k_bwd_layer(BwdArgs a) {
+  __shared__ __attribute__((aligned(16))) __bf16 dzs[BW_R * BW_LN], hs[BW_R * BW_LH], os[BW_R * BW_LO];
+  const int t = threadIdx.x, l = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int m16 = l & 15, g = l >> 4;
+  // the workgroups of a row range run on one XCD, where they share dZ through its L2
+  const int ny = a.K / BW_C, lb = (int)xcd_remap(blockIdx.x, gridDim.x), sp = lb / ny, yi = lb % ny;
+  const int k0 = yi * BW_C;
+  // 16-byte pieces, BW_T apart: of a block of dZ (contiguous), and of H's columns of this workgroup
+  constexpr int PD = BW_R * N / 8 / BW_T, PH = BW_R * BW_C / 8 / BW_T, RN = N / 8, RH = BW_C / 8;
+  bf8 rd[PD], rq[PH];
+  auto at = [&](int j, int per_row, int ld) {  // offset of this thread's piece j in rows of stride ld
+    const int c = t + BW_T * j;
+    return (c / per_row) * ld + (c % per_row) * 8;
+  };
+  auto load = [&](int b) {
+    const __bf16* dz = a.dZ + (size_t)b * BW_R * N;
+    const __bf16* h = a.H + (size_t)b * BW_R * a.K + k0;
+#pragma unroll
+    for (int j = 0; j < PD; ++j)
+      rd[j] = *(const bf8*)(dz + 8 * (t + BW_T * j));
+#pragma unroll
+    for (int j = 0; j < PH; ++j)
+      rq[j] = *(const bf8*)(h + at(j, RH, a.K));
+  };
+  f4 dw[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dw[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  double cs[4] = {0.0, 0.0, 0.0, 0.0};
+  // wavefront's part of dZ_below: rows 32 (w / 2), columns 32 (w % 2); of dW: all rows, columns 64 w
+  const int wr = w >> 1, wc = w & 1;
+  const bool on1 = a.dZb, on2 = 64 * w < N;
+  // the wavefront's operand of dZ W^T, all of it: 32 columns by N
+  bf8 wf[N / 32][2];
+#pragma unroll
+  for (int n = 0; n < N / 32; ++n)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      if (on1) wf[n][j] = *(const bf8*)(a.W + (size_t)(k0 + 32 * wc + 16 * j + m16) * N + 32 * n + 8 * g);
+  int b = sp * a.chunk;
+  const int be = min(a.M / BW_R, b + a.chunk);
+  if (b < be) load(b);
+  for (; b < be; ++b) {
+#pragma unroll
+    for (int j = 0; j < PD; ++j)
+      *(bf8*)(dzs + at(j, RN, BW_LN)) = rd[j];
+#pragma unroll
+    for (int j = 0; j < PH; ++j)
+      *(bf8*)(hs + at(j, RH, BW_LH)) = rq[j];
+    __syncthreads();
+    if (b + 1 < be) load(b + 1);
+    f4 acc[2][2];
+    if (on1) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int n = 0; n < N / 32; ++n)
+        {
+          bf8 av[2];
+#pragma unroll
+          for (int i = 0; i < 2; ++i) av[i] = *(const bf8*)(dzs + (32 * wr + 16 * i + m16) * BW_LN + 32 * n + 8 * g);
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], wf[n][j], acc[i][j], 0, 0, 0);
+        }
+    }
+    if (on2) {
+#pragma unroll
+      for (int r = 0; r < BW_R; r += 32) {
+        bf8 av[4], bv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          av[i] = ld_tr(hs, BW_LH, r + 8 * g, 16 * i, m16);
+          bv[i] = ld_tr(dzs, BW_LN, r + 8 * g, 64 * w + 16 * i, m16);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) dw[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[j], dw[i][j], 0, 0, 0);
+      }
+    }
+    // column sums: lane's column of each 64-column set of this workgroup, 16 rows
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = 64 * (yi + ny * u) + l;
+      if (c < N)
+#pragma unroll 8
+        for (int r = 0; r < 16; ++r)
+          cs[u] += (double)__uint_as_float((unsigned)*(const unsigned short*)(dzs + (16 * w + r) * BW_LN + c) << 16);
+    }
+    if (on1) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int row = 32 * wr + 16 * i + 4 * g + q, col = 32 * wc + 16 * j + m16;
+            const float h = bf2f(hs[row * BW_LH + col]);
+            float v = acc[i][j][q];
+            v *= 1.0f - h * h;
+            os[row * BW_LO + col] = (__bf16)v;
+          }
+    }
+    __syncthreads();  // this block's tiles are read; os is whole
+    if (a.dZb)
+#pragma unroll
+      for (int j = 0; j < PH; ++j)
+        *(bf8*)(a.dZb + (size_t)b * BW_R * a.K + k0 + at(j, RH, a.K)) = *(const bf8*)(os + at(j, RH, BW_LO));
+  }
+  if (on2) {
+    float* out = a.part + ((size_t)sp * a.K + k0) * N + 64 * w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[(size_t)(16 * i + 4 * g + q) * N + 16 * j + m16] = dw[i][j][q];
+  }
+  __syncthreads();
+  double* red = reinterpret_cast<double*>(dzs);  // 4 wavefronts x 256
+#pragma unroll
+  for (int u = 0; u < 4; ++u) red[256 * w + 64 * u + l] = cs[u];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int c = 64 * (yi + ny * u) + l;
+    if (w == 0 && c < N)
+      a.dbpart[(size_t)sp * N + c] =
+          (red[64 * u + l] + red[256 + 64 * u + l]) + (red[512 + 64 * u + l] + red[768 + 64 * u + l]);
+  }
+}
+
+// dW and db of every trunk layer from k_bwd_layer's partials, added in order: 256
+// entries of a dW per workgroup, or one db
+struct BwdSum {
+  int L;
+  int tile0[FW_MAXL + 1];  // first workgroup of a layer
+  int KN[FW_MAXL], N[FW_MAXL], splits[FW_MAXL], chunk[FW_MAXL];
+  size_t part[FW_MAXL], dbpart[FW_MAXL];  // offsets of its partials
+  size_t offW[FW_MAXL], offb[FW_MAXL];
+};
+template <typename R>
+__device__ __forceinline__ R sum_in_order(const R* __restrict__ p, int n, size_t stride) {
+  R v = 0;
+  for (int z0 = 0; z0 < n; z0 += 32) {
+    R x[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) x[u] = z0 + u < n ? p[(size_t)(z0 + u) * stride] : R(0);
+#pragma unroll
+    for (int u = 0; u < 32; ++u) v += x[u];
+  }
+  return v;
+}
+__global__ __launch_bounds__(256) void k_bwd_reduce(BwdSum a, const float* __restrict__ part,
+                                                    const double* __restrict__ dbpart, float* __restrict__ grad) {
+  int l = 0;
+  while ((int)blockIdx.x >= a.tile0[l + 1]) ++l;
+  const int e = (blockIdx.x - a.tile0[l]) * 256 + threadIdx.x, KN = a.KN[l], N = a.N[l];
+  if (e < KN) grad[a.offW[l] + e] = sum_in_order(part + a.part[l] + e, a.splits[l], KN);
+  else if (e - KN < N) grad[a.offb[l] + e - KN] = (float)sum_in_order(dbpart + a.dbpart[l] + e - KN, a.splits[l], N);
 }
 
 // sum of split-k slices in a fixed order, then the epilogue (and the transposed copy)
@@ -402,16 +616,29 @@ __global__ __launch_bounds__(256) void k_rowsum(const __bf16* __restrict__ D, lo
   if (threadIdx.x == 0) out[blockIdx.x] = (float)a;
 }
 
-// Branch inputs of the batch: rows idx[step S + s] of the dataset (bf16, padded), and the transpose
+// Branch inputs of the batch: rows idx[step S + s] of the dataset (bf16, padded),
+// and the transpose, 64 columns of 64 rows per workgroup, turned in LDS
 __global__ __launch_bounds__(256) void k_gather(const __bf16* __restrict__ F, long ldf, const int* __restrict__ idx,
                                                 const int* __restrict__ step, int S, __bf16* __restrict__ out,
                                                 __bf16* __restrict__ outT) {
-  const int s = blockIdx.y;
-  const int src = idx[(long)step[0] * S + s];
-  for (long c = blockIdx.x * 256L + threadIdx.x; c < ldf; c += (long)gridDim.x * 256) {
-    const __bf16 v = F[(long)src * ldf + c];
-    out[(long)s * ldf + c] = v;
-    outT[c * S + s] = v;
+  __shared__ __bf16 tile[64][64 + 2];
+  const int t = threadIdx.x, c0 = blockIdx.x * 64, s0 = blockIdx.y * 64;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int e = t + 256 * j, r = e >> 3, kq = (e & 7) * 8;
+    const bf8 v = *(const bf8*)(F + (long)idx[(long)step[0] * S + s0 + r] * ldf + c0 + kq);
+    *(bf8*)(out + (long)(s0 + r) * ldf + c0 + kq) = v;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) tile[r][kq + u] = v[u];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int e = t + 256 * j, c = e >> 3, rq = (e & 7) * 8;
+    bf8 v;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = tile[rq + u][c];
+    *(bf8*)(outT + (long)(c0 + c) * S + s0 + rq) = v;
   }
 }
 
@@ -425,95 +652,273 @@ __global__ void k_to_bc(const __bf16* __restrict__ B, int S, int p, __bf16* __re
   BcT[(long)c * 2 * S + r] = v;
 }
 
-// dB (S x 2p) and its transpose (2p x S), bf16, from dBc (2S x p, fp32)
-__global__ void k_from_dbc(const float* __restrict__ dBc, int S, int p, __bf16* __restrict__ dB,
-                           __bf16* __restrict__ dBT) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= 2 * S * p) return;
-  const int s = e / (2 * p), c = e % (2 * p);
-  const __bf16 v = (__bf16)(c < p ? dBc[(long)s * p + c] : dBc[(long)(S + s) * p + (c - p)]);
-  dB[e] = v;
-  dBT[(long)c * S + s] = v;
-}
+// ---- output product, loss and its gradient ------------------------------------------
+// U = Bc T^T is formed twice instead of stored: GRAD = false sums ||U_s - Y_s||^2
+// and ||Y_s||^2 (fp64), GRAD = true, with the weights those give, forms dU = (U -
+// Y) w_s (bf16) and from it dT = dU^T Bc and the partials of dBc = dU T, all of a
+// 64-point tile in LDS: T and the labels are read once per pass and only dT is
+// written (84 and 112 MB at P = 110592, S = 64, p = 128).  Workgroups of eight
+// wavefronts take ranges of tiles; wavefront w forms U for samples 16 (w %
+// 4) .. + 15, Re and Im, at points 32 (w / 4) .. + 31, so that a label's two parts
+// meet in one lane.  The operands that run along points are read from LDS
+// transposed, as in k_bwd_layer; U, dU, dT and dBc are the values of k_gemm_nt bit
+// for bit.
+// As seven launches with U (fp32), dU, its transpose and T^T stored, this part
+// of a step took 151 us; 76 now.
+constexpr int OL_P = 64;  // points per tile
+struct OutArgs {
+  int P, chunk;                // points; tiles per workgroup
+  const __bf16 *T, *Bc, *BcT;  // P x p; 2S x p and its transpose
+  const float2* Y;             // labels, n x P
+  const int *idx, *step;
+  const float* w;              // GRAD: the samples' weights
+  double* lpart;               // !GRAD: S x gridDim x 2
+  __bf16* dT;                  // GRAD: P x p
+  float* part;                 // GRAD: gridDim x 2S x p
+};
 
-// per (sample, chunk): ||U_s - Y_s||^2 and ||Y_s||^2 over the chunk's points (fp64)
-__global__ __launch_bounds__(256) void k_loss_part(const float* __restrict__ Ut, const float2* __restrict__ Y,
-                                                   const int* __restrict__ idx, const int* __restrict__ step, int S,
-                                                   int P, int chunk, double* __restrict__ part) {
-  __shared__ double sh[32];
-  const int s = blockIdx.y;
-  const long src = idx[(long)step[0] * S + s];
-  const int p0 = blockIdx.x * chunk, p1 = min(P, p0 + chunk);
-  double dn = 0.0, yn = 0.0;
-  for (int q = p0 + threadIdx.x; q < p1; q += 256) {
-    const float2 y = Y[src * P + q];
-    const double dr = (double)Ut[(long)s * P + q] - y.x, di = (double)Ut[(long)(S + s) * P + q] - y.y;
-    dn += dr * dr + di * di;
-    yn += (double)y.x * y.x + (double)y.y * y.y;
-  }
-  dn = block_sum(dn, sh);
-  yn = block_sum(yn, sh);
-  if (threadIdx.x == 0) {
-    part[((long)s * gridDim.x + blockIdx.x) * 2] = dn;
-    part[((long)s * gridDim.x + blockIdx.x) * 2 + 1] = yn;
-  }
-}
-
-// per-sample norms -> weights w_s = 1 / (S ||U_s - Y_s|| ||Y_s||); loss[step] = mean relative error
-__global__ void k_loss_final(const double* __restrict__ part, int S, int nch, const int* __restrict__ step,
-                             float* __restrict__ w, float* __restrict__ loss) {
-  __shared__ double rel[256];
-  const int s = threadIdx.x;
-  if (s < S) {
-    double dn = 0.0, yn = 0.0;
-    for (int c = 0; c < nch; ++c) {
-      dn += part[((long)s * nch + c) * 2];
-      yn += part[((long)s * nch + c) * 2 + 1];
+template <int S, int PP, bool GRAD>
+__global__ __launch_bounds__(512) void k_out(OutArgs a) {
+  constexpr int NG = S / 64, KT = PP / 32, LT = PP + 16, LD = 2 * S + 16, LO = PP + 8, PT = OL_P * PP / 8 / 512;
+  static_assert(OL_P * PP / 8 % 512 == 0, "pieces per thread");
+  __shared__ __attribute__((aligned(16))) __bf16 ts[OL_P * LT], dus[GRAD ? OL_P * LD : 1], os[GRAD ? OL_P * LO : 1];
+  const int t = threadIdx.x, l = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int m16 = l & 15, g = l >> 4, sg = w & 3, ph = w >> 2;
+  const int nt = a.P / OL_P;
+  bf8 rt[PT];
+  auto load_t = [&](int b) {
+    const __bf16* p = a.T + (size_t)b * OL_P * PP;
+#pragma unroll
+    for (int j = 0; j < PT; ++j) rt[j] = *(const bf8*)(p + 8 * (t + 512 * j));
+  };
+  // this wavefront's rows of Bc, and its samples' label rows and weights
+  bf8 bc[NG][2][KT];
+  const float2* y[NG][4];
+  float ws[NG][4];
+#pragma unroll
+  for (int n = 0; n < NG; ++n) {
+    const int s0 = 64 * n + 16 * sg;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int k = 0; k < KT; ++k) bc[n][c][k] = *(const bf8*)(a.Bc + (size_t)(c * S + s0 + m16) * PP + 32 * k + 8 * g);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int s = s0 + 4 * g + q;
+      y[n][q] = a.Y + (size_t)a.idx[(size_t)a.step[0] * S + s] * a.P + 32 * ph + m16;
+      ws[n][q] = GRAD ? a.w[s] : 0.f;
     }
+  }
+  float2 yv[NG][2][4];
+  auto load_y = [&](int b) {
+#pragma unroll
+    for (int n = 0; n < NG; ++n)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) yv[n][j][q] = y[n][q][(size_t)b * OL_P + 16 * j];
+  };
+  double dn[NG][4], yn[NG][4];
+#pragma unroll
+  for (int n = 0; n < NG; ++n)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) dn[n][q] = yn[n][q] = 0.0;
+  // dT: points 32 (w / 4), columns (p / 4) (w % 4); dBc: rows (2S / 4) (w / 2), columns (p / 2) (w % 2)
+  constexpr int CT = PP / 64, KR = 2 * S / 32, RT = 2 * S / 64, CN = PP / 32;
+  bf8 bt[GRAD ? KR : 1][CT];
+  f4 dbc[GRAD ? RT : 1][CN];
+  if (GRAD) {
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+#pragma unroll
+      for (int j = 0; j < CT; ++j)
+        bt[k][j] = *(const bf8*)(a.BcT + (size_t)((PP / 4) * sg + 16 * j + m16) * (2 * S) + 32 * k + 8 * g);
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int j = 0; j < CN; ++j) dbc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  }
+  int b = blockIdx.x * a.chunk;
+  const int be = min(nt, b + a.chunk);
+  if (b < be) {
+    load_t(b);
+    load_y(b);
+  }
+  for (; b < be; ++b) {
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+      const int c = t + 512 * j;
+      *(bf8*)(ts + (c / (PP / 8)) * LT + (c % (PP / 8)) * 8) = rt[j];
+    }
+    __syncthreads();
+    const bool more = b + 1 < be;
+    if (more) load_t(b + 1);
+#pragma unroll
+    for (int n = 0; n < NG; ++n) {
+      f4 u[2][2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) u[c][j] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < KT; ++k) {
+        bf8 tv[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) tv[j] = *(const bf8*)(ts + (32 * ph + 16 * j + m16) * LT + 32 * k + 8 * g);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) u[c][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bc[n][c][k], tv[j], u[c][j], 0, 0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        if (!GRAD) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float2 v = yv[n][j][q];
+            const double dr = (double)u[0][j][q] - v.x, di = (double)u[1][j][q] - v.y;
+            dn[n][q] += dr * dr + di * di;
+            yn[n][q] += (double)v.x * v.x + (double)v.y * v.y;
+          }
+        } else {
+          __bf16 re[4], im[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            re[q] = (__bf16)((u[0][j][q] - yv[n][j][q].x) * ws[n][q]);
+            im[q] = (__bf16)((u[1][j][q] - yv[n][j][q].y) * ws[n][q]);
+          }
+          __bf16* d = dus + (32 * ph + 16 * j + m16) * LD + 64 * n + 16 * sg + 4 * g;
+          typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+          *(bf4*)d = bf4{re[0], re[1], re[2], re[3]};
+          *(bf4*)(d + S) = bf4{im[0], im[1], im[2], im[3]};
+        }
+      }
+    }
+    if (more) load_y(b + 1);
+    __syncthreads();  // T is read (GRAD = false), dU is whole
+    if (!GRAD) continue;
+    f4 o[2][CT];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < CT; ++j) o[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+      bf8 dv[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) dv[i] = *(const bf8*)(dus + (32 * ph + 16 * i + m16) * LD + 32 * k + 8 * g);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) o[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(dv[i], bt[k][j], o[i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < CT; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          os[(32 * ph + 16 * i + 4 * g + q) * LO + (PP / 4) * sg + 16 * j + m16] = (__bf16)o[i][j][q];
+#pragma unroll
+    for (int r = 0; r < OL_P; r += 32) {
+      bf8 av[RT], bv[CN];
+#pragma unroll
+      for (int i = 0; i < RT; ++i) av[i] = ld_tr(dus, LD, r + 8 * g, (S / 2) * (w >> 1) + 16 * i, m16);
+#pragma unroll
+      for (int j = 0; j < CN; ++j) bv[j] = ld_tr(ts, LT, r + 8 * g, (PP / 2) * (w & 1) + 16 * j, m16);
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CN; ++j) dbc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[j], dbc[i][j], 0, 0, 0);
+    }
+    __syncthreads();  // the tiles are read, os is whole
+#pragma unroll
+    for (int j = 0; j < PT; ++j) {
+      const int c = t + 512 * j;
+      *(bf8*)(a.dT + (size_t)b * OL_P * PP + 8 * c) = *(const bf8*)(os + (c / (PP / 8)) * LO + (c % (PP / 8)) * 8);
+    }
+  }
+  if (GRAD) {
+    float* out = a.part + (size_t)blockIdx.x * 2 * S * PP;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int j = 0; j < CN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          out[(size_t)((S / 2) * (w >> 1) + 16 * i + 4 * g + q) * PP + (PP / 2) * (w & 1) + 16 * j + m16] = dbc[i][j][q];
+  } else {
+    // over the 16 lanes of a row, then the two point halves
+    __shared__ double red[2][S][2];
+#pragma unroll
+    for (int n = 0; n < NG; ++n)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        double d = dn[n][q], v = yn[n][q];
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) {
+          d += __shfl_xor(d, off, 64);
+          v += __shfl_xor(v, off, 64);
+        }
+        if (m16 == 0) {
+          red[ph][64 * n + 16 * sg + 4 * g + q][0] = d;
+          red[ph][64 * n + 16 * sg + 4 * g + q][1] = v;
+        }
+      }
+    __syncthreads();
+    if (t < 2 * S) {
+      const int s = t >> 1, k = t & 1;
+      a.lpart[((size_t)s * gridDim.x + blockIdx.x) * 2 + k] = red[0][s][k] + red[1][s][k];
+    }
+  }
+}
+
+// per-sample norms -> weights w_s = 1 / (S ||U_s - Y_s|| ||Y_s||); loss[step] = mean
+// relative error.  1024 / S threads sum a sample's partials.
+__global__ __launch_bounds__(1024) void k_loss_final(const double* __restrict__ part, int S, int nch,
+                                                     const int* __restrict__ step, float* __restrict__ w,
+                                                     float* __restrict__ loss) {
+  __shared__ double rel[128];
+  const int per = 1024 / S, s = threadIdx.x / per, k = threadIdx.x % per;
+  double dn = 0.0, yn = 0.0;
+  const double2* p = reinterpret_cast<const double2*>(part) + (size_t)s * nch;
+  for (int c0 = k; c0 < nch; c0 += 8 * per) {
+    double2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = c0 + u * per < nch ? p[c0 + u * per] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      dn += v[u].x;
+      yn += v[u].y;
+    }
+  }
+  for (int off = per >> 1; off > 0; off >>= 1) {
+    dn += __shfl_xor(dn, off, 64);
+    yn += __shfl_xor(yn, off, 64);
+  }
+  if (k == 0) {
     dn = sqrt(dn);
     yn = sqrt(yn);
     rel[s] = dn / yn;
     w[s] = (float)(dn > 0.0 ? 1.0 / (S * dn * yn) : 0.0);
   }
   __syncthreads();
-  if (s == 0) {
+  if (threadIdx.x == 0) {
     double a = 0.0;
     for (int i = 0; i < S; ++i) a += rel[i];
     loss[step[0]] = (float)(a / S);
   }
 }
 
-// dUt (2S x P, bf16) = (Ut - Y) w_s, and its transpose dUtT (P x 2S): a workgroup
-// takes 64 points, reads the 2S rows coalesced and writes the point-major copy
-// through LDS
-__global__ __launch_bounds__(256) void k_dU(const float* __restrict__ Ut, const float2* __restrict__ Y,
-                                            const int* __restrict__ idx, const int* __restrict__ step,
-                                            const float* __restrict__ w, int S, int P, __bf16* __restrict__ dUt,
-                                            __bf16* __restrict__ dUtT) {
-  __shared__ __attribute__((aligned(16))) __bf16 tile[64 * (256 + 8)];
-  const int q0 = blockIdx.x * 64, t = threadIdx.x, pl = t & 63;
-  const int R = 2 * S, ld = R + 8;
-  for (int s = t >> 6; s < S; s += 4) {
-    const long src = idx[(long)step[0] * S + s];
-    const float ws = w[s];
-    const int q = q0 + pl;
-    __bf16 re = (__bf16)0.0f, im = (__bf16)0.0f;
-    if (q < P) {
-      const float2 y = Y[src * P + q];
-      re = (__bf16)((Ut[(long)s * P + q] - y.x) * ws);
-      im = (__bf16)((Ut[(long)(S + s) * P + q] - y.y) * ws);
-      dUt[(long)s * P + q] = re;
-      dUt[(long)(S + s) * P + q] = im;
-    }
-    tile[pl * ld + s] = re;
-    tile[pl * ld + S + s] = im;
-  }
-  __syncthreads();
-  const int chunks = R / 8;
-  for (int c = t; c < 64 * chunks; c += 256) {
-    const int pt = c / chunks, rq = (c % chunks) * 8;
-    if (q0 + pt < P) *(bf8*)(dUtT + (long)(q0 + pt) * R + rq) = *(const bf8*)(tile + pt * ld + rq);
-  }
+// dB (S x 2p) and its transpose (2p x S), bf16, from the partials of dBc (2S x p),
+// added in order
+__global__ __launch_bounds__(64) void k_from_dbc(const float* __restrict__ part, int nparts, int S, int p,
+                                                 __bf16* __restrict__ dB, __bf16* __restrict__ dBT) {
+  const int e = blockIdx.x * 64 + threadIdx.x, n = 2 * S * p;
+  const __bf16 r = (__bf16)sum_in_order(part + e, nparts, n);
+  const int row = e / p, s = row % S, col = e % p + (row < S ? 0 : p);
+  dB[s * 2 * p + col] = r;
+  dBT[(long)col * S + s] = r;
 }
 
 // weight matrices inside the flat parameter array (Kp x N row-major at off,
@@ -655,11 +1060,12 @@ struct don_trainer_s {
   size_t nparam = 0;
   int max_steps = 0;
   Buffer master, grad, mom, var, wbf, wtb;  // flat fp32 parameters, Adam moments, bf16 W and W^T copies
-  Buffer X, XT;                             // P x Kp trunk inputs (bf16) and transpose
+  Buffer X;                                 // P x Kp trunk inputs (bf16)
   Buffer Fb, FbT;                           // S x Kp branch inputs of the batch and transpose
   Acts ba, ta;                              // branch and trunk activations
-  Buffer dz[2], dzT[2], bdz[2], bdzT[2];    // backward ping-pong (trunk, branch)
-  Buffer Bc, BcT, Ut, dUt, dUtT, dBc, part, lpart, wv, ctr, losses, idx;
+  Buffer dz[2], bdz[2], bdzT[2];            // backward ping-pong (trunk, branch)
+  Buffer wpart, dbpart;                     // k_bwd_layer's partials of every layer
+  Buffer Bc, BcT, part, lpart, wv, ctr, losses, idx;
   Buffer Fdata;                             // n x Kb_pad bf16
   const float2* Y = nullptr;                // n x P complex64 labels (caller's)
   int ndata = 0;
@@ -668,9 +1074,6 @@ struct don_trainer_s {
   // the branch MLP runs on st2, beside the trunk on st (forked and joined by events)
   hipStream_t st2 = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  // the trunk's bias gradients (row sums of dZ^T) run on st3 beside its weight products
-  hipStream_t st3 = nullptr;
-  hipEvent_t ev_rs = nullptr, ev_rsj = nullptr;
   Buffer bpart;  // split-k partials of the branch products (the trunk's use part)
   hipGraphExec_t step_exec = nullptr;   // one step
   hipGraphExec_t multi_exec = nullptr;  // GRAPH_STEPS steps (fewer gaps between graph launches)
@@ -679,14 +1082,10 @@ struct don_trainer_s {
     if (multi_exec) (void)hipGraphExecDestroy(multi_exec);
     if (ev_fork) (void)hipEventDestroy(ev_fork);
     if (ev_join) (void)hipEventDestroy(ev_join);
-    if (ev_rs) (void)hipEventDestroy(ev_rs);
-    if (ev_rsj) (void)hipEventDestroy(ev_rsj);
     if (st2) (void)hipStreamDestroy(st2);
-    if (st3) (void)hipStreamDestroy(st3);
     if (st) (void)hipStreamDestroy(st);
-    for (Buffer* b : {&master, &grad, &mom, &var, &wbf, &wtb, &X, &XT, &Fb, &FbT, &ba.h, &ba.hT, &ta.h, &ta.hT, &dz[0],
-                      &dz[1], &dzT[0], &dzT[1], &bdz[0], &bdz[1], &bdzT[0], &bdzT[1], &Bc, &BcT, &Ut, &dUt, &dUtT,
-                      &dBc, &part, &bpart, &lpart, &wv, &ctr, &losses, &idx, &Fdata})
+    for (Buffer* b : {&master, &grad, &mom, &var, &wbf, &wtb, &X, &Fb, &FbT, &ba.h, &ba.hT, &ta.h, &ta.hT, &dz[0],
+                      &dz[1], &wpart, &dbpart, &bdz[0], &bdz[1], &bdzT[0], &bdzT[1], &Bc, &BcT, &part, &bpart, &lpart, &wv, &ctr, &losses, &idx, &Fdata})
       b->release();
   }
 };
@@ -747,7 +1146,7 @@ void mlp_fwd(don_trainer_s* t, std::vector<Layer>& L, const __bf16* H0, int M, A
 // forward through layers first .. of one MLP in one launch (k_mlp_fwd); the
 // input is H0 for first = 0, else the output of layer first - 1
 void mlp_fwd_fused(don_trainer_s* t, std::vector<Layer>& L, const __bf16* H0, int M, Acts& a, hipStream_t st,
-                   int first = 0) {
+                   int first = 0, bool transposes = true) {
   FwdArgs f{};
   f.L = (int)L.size() - first;
   f.M = M;
@@ -759,59 +1158,99 @@ void mlp_fwd_fused(don_trainer_s* t, std::vector<Layer>& L, const __bf16* H0, in
     f.wt[q] = (const __bf16*)t->wtb.ptr + y.offW;
     f.bias[q] = (const float*)t->master.ptr + y.offb;
     f.h[q] = (__bf16*)a.h.ptr + a.off[first + q];
-    f.hT[q] = (__bf16*)a.hT.ptr + a.off[first + q];
+    f.hT[q] = transposes ? (__bf16*)a.hT.ptr + a.off[first + q] : nullptr;
   }
   hipLaunchKernelGGL(k_mlp_fwd, dim3((M + TM - 1) / TM), dim3(256), 0, st, f);
 }
 
-// backward through one MLP given dZ of its last layer (row-major dz[0], transposed dzT[0])
-// side (optional): stream for each layer's weight and bias gradients, forked
-// from st once the layer's dZ is there, so they run beside the product that
-// forms the next dZ; st waits for a layer's side work before it overwrites the
-// dZ buffers that work reads (two layers on), and at the end
+// backward through the branch given dZ of its last layer (row-major dz[0],
+// transposed dzT[0]), one product each for dW and the next dZ
 void mlp_bwd(don_trainer_s* t, std::vector<Layer>& L, const __bf16* H0T, int M, Acts& a, Buffer* dz, Buffer* dzT,
-             hipStream_t st, float* part, hipStream_t side = nullptr) {
+             hipStream_t st, float* part) {
   const __bf16* wb = (const __bf16*)t->wbf.ptr;
   float* g = (float*)t->grad.ptr;
   const __bf16* h = (const __bf16*)a.h.ptr;
   const __bf16* hT = (const __bf16*)a.hT.ptr;
-  hipStream_t gs = side ? side : st;  // stream of the gradient products
   int cur = 0;
-  bool pending = false;  // side work of the previous layer not yet waited for
   for (int li = (int)L.size() - 1; li >= 0; --li) {
     const Layer& y = L[li];
     const __bf16* inT = li == 0 ? H0T : hT + a.off[li - 1];
     __bf16* d = (__bf16*)dz[cur].ptr;
     __bf16* dT = (__bf16*)dzT[cur].ptr;
-    if (side) {
-      (void)hipEventRecord(t->ev_rs, st);
-      (void)hipStreamWaitEvent(side, t->ev_rs, 0);
-    }
     // db = row sums of dZ^T
-    hipLaunchKernelGGL(k_rowsum, dim3(y.N), dim3(256), 0, gs, (const __bf16*)dT, (long)M, g + y.offb);
+    hipLaunchKernelGGL(k_rowsum, dim3(y.N), dim3(256), 0, st, (const __bf16*)dT, (long)M, g + y.offb);
     // dW = H^T dZ (Kp x N): A = H^T (Kp x M), B = dZ^T (N x M), reduction over the M rows
     int sp = splits_for(y.Kp, y.N, M, 512);
     while ((size_t)sp * y.Kp * y.N > t->part_floats && sp > 1) --sp;
-    gemm(gs, inT, M, dT, M, y.Kp, y.N, M, g + y.offW, y.N, EP_F32, nullptr, nullptr, nullptr, 0, sp, part);
+    gemm(st, inT, M, dT, M, y.Kp, y.N, M, g + y.offW, y.N, EP_F32, nullptr, nullptr, nullptr, 0, sp, part);
     if (li > 0) {
       // dZ_below = (dZ W^T) * (1 - H_below^2): A = dZ (M x N), B = W (Kp x N, n-major = k-contiguous)
       const Layer& z = L[li - 1];
-      __bf16* dn = (__bf16*)dz[1 - cur].ptr;
-      __bf16* dnT = (__bf16*)dzT[1 - cur].ptr;
-      // dn / dnT held the previous layer's dZ, read by that layer's side work
-      if (pending) (void)hipStreamWaitEvent(st, t->ev_rsj, 0);
-      if (side) {
-        (void)hipEventRecord(t->ev_rsj, side);  // this layer's side work, waited for one layer on
-        pending = true;
-      }
-      gemm(st, d, y.N, wb + y.offW, y.N, M, z.N, y.N, dn, z.N, EP_DTANH_BF16, nullptr, h + a.off[li - 1], dnT, M);
+      gemm(st, d, y.N, wb + y.offW, y.N, M, z.N, y.N, dz[1 - cur].ptr, z.N, EP_DTANH_BF16, nullptr, h + a.off[li - 1],
+           (__bf16*)dzT[1 - cur].ptr, M);
       cur = 1 - cur;
-    } else if (side) {
-      (void)hipEventRecord(t->ev_rsj, side);
-      pending = true;
     }
   }
-  if (pending) (void)hipStreamWaitEvent(st, t->ev_rsj, 0);
+}
+
+// where each trunk layer's partials and gradients are, and the partials' total sizes
+BwdSum bwd_sum(const don_trainer_s* t, size_t* parts, size_t* dbparts) {
+  BwdSum a{};
+  *parts = *dbparts = 0;
+  for (const Layer& y : t->tl) {
+    const int l = a.L++;
+    // row ranges: about 512 workgroups of 128 x 128 entries of dW (at 256 x 256, 496
+    // of 64 columns, two on each CU but eight: the branch's small products run there)
+    const int nblk = t->P / BW_R;
+    int sp = splits_for(y.Kp, y.N, t->P, 512);
+    if (sp > nblk) sp = nblk;
+    a.chunk[l] = (nblk + sp - 1) / sp;
+    a.splits[l] = (nblk + a.chunk[l] - 1) / a.chunk[l];
+    a.KN[l] = y.Kp * y.N;
+    a.N[l] = y.N;
+    a.part[l] = *parts;
+    a.dbpart[l] = *dbparts;
+    a.offW[l] = y.offW;
+    a.offb[l] = y.offb;
+    a.tile0[l + 1] = a.tile0[l] + (a.KN[l] + y.N + 255) / 256;
+    *parts += (size_t)a.splits[l] * a.KN[l];
+    *dbparts += (size_t)a.splits[l] * y.N;
+  }
+  return a;
+}
+
+// backward through the trunk given dZ of its last layer in dz[0]: one launch
+// per layer, then one that sums every layer's partials (beside the layers on
+// another stream the sums would be free, but each dependency between queues
+// costs 5 to 9 us)
+void trunk_bwd(don_trainer_s* t) {
+  const __bf16* h = (const __bf16*)t->ta.h.ptr;
+  size_t np, nd;
+  const BwdSum sum = bwd_sum(t, &np, &nd);
+  int cur = 0;
+  for (int li = sum.L - 1; li >= 0; --li) {
+    const Layer& y = t->tl[li];
+    BwdArgs a;
+    a.M = t->P;
+    a.K = y.Kp;
+    a.chunk = sum.chunk[li];
+    a.dZ = (const __bf16*)t->dz[cur].ptr;
+    a.H = li ? h + t->ta.off[li - 1] : (const __bf16*)t->X.ptr;
+    a.W = (const __bf16*)t->wbf.ptr + y.offW;
+    a.dZb = li ? (__bf16*)t->dz[1 - cur].ptr : nullptr;
+    a.part = (float*)t->wpart.ptr + sum.part[li];
+    a.dbpart = (double*)t->dbpart.ptr + sum.dbpart[li];
+    const dim3 grid(sum.splits[li] * (y.Kp / BW_C));
+    switch (y.N) {
+      case 64: hipLaunchKernelGGL(k_bwd_layer<64>, grid, dim3(BW_T), 0, t->st, a); break;
+      case 128: hipLaunchKernelGGL(k_bwd_layer<128>, grid, dim3(BW_T), 0, t->st, a); break;
+      case 192: hipLaunchKernelGGL(k_bwd_layer<192>, grid, dim3(BW_T), 0, t->st, a); break;
+      default: hipLaunchKernelGGL(k_bwd_layer<256>, grid, dim3(BW_T), 0, t->st, a);
+    }
+    cur = 1 - cur;
+  }
+  hipLaunchKernelGGL(k_bwd_reduce, dim3(sum.tile0[sum.L]), dim3(256), 0, t->st, sum, (const float*)t->wpart.ptr,
+                     (const double*)t->dbpart.ptr, (float*)t->grad.ptr);
 }
 
 // Adam step on st (parameters, moments, both bf16 copies)
@@ -841,6 +1280,27 @@ void join(don_trainer_s* t) {
   (void)hipStreamWaitEvent(t->st, t->ev_join, 0);
 }
 
+constexpr int OUT_MAXB = 512;  // workgroups of the loss pass
+// workgroups (and tiles of each) of the gradient pass: the point ranges over
+// which dBc is accumulated in fp32 before its partials are added in order.  dBc
+// is rounded to bf16, so its sums keep this order.
+int out_splits(int S, int p, int P, int* chunk) {
+  const int tiles = P / OL_P;
+  int n = splits_for(2 * S, p, P, 128);
+  if (n > tiles) n = tiles;
+  *chunk = (tiles + n - 1) / n;
+  return (tiles + *chunk - 1) / *chunk;
+}
+
+// k_out by batch (64 or 128) and trunk outputs (64 or 128)
+template <bool GRAD>
+void out_launch(int S, int p, int blocks, hipStream_t st, const OutArgs& a) {
+  if (S == 64 && p == 64) hipLaunchKernelGGL((k_out<64, 64, GRAD>), dim3(blocks), dim3(512), 0, st, a);
+  else if (S == 64) hipLaunchKernelGGL((k_out<64, 128, GRAD>), dim3(blocks), dim3(512), 0, st, a);
+  else if (p == 64) hipLaunchKernelGGL((k_out<128, 64, GRAD>), dim3(blocks), dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((k_out<128, 128, GRAD>), dim3(blocks), dim3(512), 0, st, a);
+}
+
 void train_step(don_trainer_s* t, bool update) {
   const int S = t->S, P = t->P, p = t->p;
   const int* ctr = (const int*)t->ctr.ptr;
@@ -850,45 +1310,36 @@ void train_step(don_trainer_s* t, bool update) {
   __bf16* FbT = (__bf16*)t->FbT.ptr;
   // the two MLPs are independent until the output product: branch on st2, trunk on st
   fork(t);
-  hipLaunchKernelGGL(k_gather, dim3(grid_for(b0.Kp) < 64 ? grid_for(b0.Kp) : 64, S), dim3(256), 0, t->st2,
+  hipLaunchKernelGGL(k_gather, dim3(b0.Kp / 64, S / 64), dim3(256), 0, t->st2,
                      (const __bf16*)t->Fdata.ptr, (long)b0.Kp, idx, ctr, S, Fb, FbT);
   // branch: the wide input layer as a split-k product, the rest in one launch
   mlp_fwd(t, t->bl, Fb, S, t->ba, t->st2, (float*)t->bpart.ptr, 1);
   if (t->bl.size() > 1) mlp_fwd_fused(t, t->bl, Fb, S, t->ba, t->st2, 1);
-  mlp_fwd_fused(t, t->tl, (const __bf16*)t->X.ptr, P, t->ta, t->st);
+  mlp_fwd_fused(t, t->tl, (const __bf16*)t->X.ptr, P, t->ta, t->st, 0, false);
   join(t);
   const size_t lb = t->bl.size() - 1, lt = t->tl.size() - 1;
   const __bf16* Bout = (const __bf16*)t->ba.h.ptr + t->ba.off[lb];
   const __bf16* T = (const __bf16*)t->ta.h.ptr + t->ta.off[lt];
-  const __bf16* TT = (const __bf16*)t->ta.hT.ptr + t->ta.off[lt];
   __bf16* Bc = (__bf16*)t->Bc.ptr;
   __bf16* BcT = (__bf16*)t->BcT.ptr;
   hipLaunchKernelGGL(k_to_bc, dim3((2 * S * p + 255) / 256), dim3(256), 0, t->st, Bout, S, p, Bc, BcT);
-  // Ut = Bc T^T (2S x P)
-  float* Ut = (float*)t->Ut.ptr;
-  gemm(t->st, Bc, p, T, p, 2 * S, P, p, Ut, P, EP_F32);
-  // loss and dUt
-  const int chunk = 4096, nch = (P + chunk - 1) / chunk;
-  hipLaunchKernelGGL(k_loss_part, dim3(nch, S), dim3(256), 0, t->st, (const float*)Ut, t->Y, idx, ctr, S, P, chunk,
-                     (double*)t->lpart.ptr);
-  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(256), 0, t->st, (const double*)t->lpart.ptr, S, nch, ctr,
+  // loss, dT (dZ of the trunk's last layer) and dB (that of the branch's)
+  OutArgs oa{P, 0, T, Bc, BcT, t->Y, idx, ctr, (const float*)t->wv.ptr, (double*)t->lpart.ptr, (__bf16*)t->dz[0].ptr,
+             (float*)t->part.ptr};
+  const int tiles = P / OL_P, ng = out_splits(S, p, P, &oa.chunk);
+  const int cg = oa.chunk;
+  oa.chunk = (tiles + OUT_MAXB - 1) / OUT_MAXB;
+  const int nl = (tiles + oa.chunk - 1) / oa.chunk;
+  out_launch<false>(S, p, nl, t->st, oa);
+  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(1024), 0, t->st, (const double*)t->lpart.ptr, S, nl, ctr,
                      (float*)t->wv.ptr, (float*)t->losses.ptr);
-  __bf16* dUt = (__bf16*)t->dUt.ptr;
-  __bf16* dUtT = (__bf16*)t->dUtT.ptr;
-  hipLaunchKernelGGL(k_dU, dim3((P + 63) / 64), dim3(256), 0, t->st, (const float*)Ut, t->Y, idx, ctr,
-                     (const float*)t->wv.ptr, S, P, dUt, dUtT);
-  // dT = dUt^T Bc (P x p): A = dUt^T (P x 2S), B = Bc^T (p x 2S) -> dZ of the trunk's last layer
-  gemm(t->st, dUtT, 2 * S, BcT, 2 * S, P, p, 2 * S, t->dz[0].ptr, p, EP_BF16, nullptr, nullptr,
-       (__bf16*)t->dzT[0].ptr, P);
-  // dBc = dUt T (2S x p): A = dUt (2S x P), B = T^T (p x P), reduction over the points
-  float* dBc = (float*)t->dBc.ptr;
-  gemm(t->st, dUt, P, TT, P, 2 * S, p, P, dBc, p, EP_F32, nullptr, nullptr, nullptr, 0, splits_for(2 * S, p, P, 128),
-       (float*)t->part.ptr);
-  hipLaunchKernelGGL(k_from_dbc, dim3((2 * S * p + 255) / 256), dim3(256), 0, t->st, (const float*)dBc, S, p,
+  oa.chunk = cg;
+  out_launch<true>(S, p, ng, t->st, oa);
+  hipLaunchKernelGGL(k_from_dbc, dim3(2 * S * p / 64), dim3(64), 0, t->st, (const float*)t->part.ptr, ng, S, p,
                      (__bf16*)t->bdz[0].ptr, (__bf16*)t->bdzT[0].ptr);
-  // trunk backward captured first (the long chain), the branch's beside it
+  // the branch's backward beside the trunk's
   fork(t);
-  mlp_bwd(t, t->tl, (const __bf16*)t->XT.ptr, P, t->ta, t->dz, t->dzT, t->st, (float*)t->part.ptr, t->st3);
+  trunk_bwd(t);
   mlp_bwd(t, t->bl, FbT, S, t->ba, t->bdz, t->bdzT, t->st2, (float*)t->bpart.ptr);
   join(t);
   if (update) {
@@ -959,21 +1410,18 @@ helm_status don_train_create(don_net net, const don_train_opts* o, const double*
   };
   if (hipStreamCreateWithFlags(&t->st, hipStreamNonBlocking) != hipSuccess ||
       hipStreamCreateWithFlags(&t->st2, hipStreamNonBlocking) != hipSuccess ||
-      hipStreamCreateWithFlags(&t->st3, hipStreamNonBlocking) != hipSuccess ||
-      hipEventCreateWithFlags(&t->ev_rs, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&t->ev_rsj, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&t->ev_fork, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&t->ev_join, hipEventDisableTiming) != hipSuccess)
     return fin(fail(HELM_E_HIP, "don_train_create: streams and events"));
   const size_t S = t->S, P = t->P;
-  auto acts = [&](Acts& a, std::vector<Layer>& L, size_t M) -> helm_status {
+  auto acts = [&](Acts& a, std::vector<Layer>& L, size_t M, bool transposes) -> helm_status {
     size_t sum = 0;
     for (auto& y : L) {
       a.off.push_back(sum);
       sum += M * y.N;
     }
     helm_status e = a.h.ensure(2 * sum);
-    return e ? e : a.hT.ensure(2 * sum);
+    return e || !transposes ? e : a.hT.ensure(2 * sum);
   };
   int maxw = 0;
   for (auto* L : {&t->bl, &t->tl})
@@ -984,20 +1432,22 @@ helm_status don_train_create(don_net net, const don_train_opts* o, const double*
   // split-k partials: every split product runs at most 512 workgroups of 128 x 128 tiles
   (void)maxkn;
   t->part_floats = std::max<size_t>((size_t)512 * TM * TN, (size_t)2 * S * t->p * 512);
-  const size_t nch = (P + 4095) / 4096;
+  const size_t nch = OUT_MAXB;
   const size_t Kb = t->bl[0].Kp, Kt = t->tl[0].Kp;
   if ((s = t->master.ensure(4 * t->nparam)) || (s = t->grad.ensure(4 * t->nparam)) ||
       (s = t->mom.ensure(4 * t->nparam)) || (s = t->var.ensure(4 * t->nparam)) || (s = t->wbf.ensure(2 * t->nparam)) ||
-      (s = t->wtb.ensure(2 * t->nparam)) || (s = t->X.ensure(2 * P * Kt)) || (s = t->XT.ensure(2 * P * Kt)) ||
-      (s = t->Fb.ensure(2 * S * Kb)) || (s = t->FbT.ensure(2 * S * Kb)) || (s = acts(t->ba, t->bl, S)) ||
-      (s = acts(t->ta, t->tl, P)))
+      (s = t->wtb.ensure(2 * t->nparam)) || (s = t->X.ensure(2 * P * Kt)) ||
+      (s = t->Fb.ensure(2 * S * Kb)) || (s = t->FbT.ensure(2 * S * Kb)) || (s = acts(t->ba, t->bl, S, true)) ||
+      (s = acts(t->ta, t->tl, P, false)))
     return fin(s);
+  size_t wp, dp;
+  (void)bwd_sum(t, &wp, &dp);
+  if ((s = t->wpart.ensure(4 * wp)) || (s = t->dbpart.ensure(8 * dp))) return fin(s);
   for (int k = 0; k < 2; ++k)
-    if ((s = t->dz[k].ensure(2 * P * maxw)) || (s = t->dzT[k].ensure(2 * P * maxw)) ||
+    if ((s = t->dz[k].ensure(2 * P * maxw)) || 
         (s = t->bdz[k].ensure(2 * S * std::max(maxw, 2 * t->p))) || (s = t->bdzT[k].ensure(2 * S * std::max(maxw, 2 * t->p))))
       return fin(s);
-  if ((s = t->Bc.ensure(2 * 2 * S * t->p)) || (s = t->BcT.ensure(2 * 2 * S * t->p)) || (s = t->Ut.ensure(4 * 2 * S * P)) ||
-      (s = t->dUt.ensure(2 * 2 * S * P)) || (s = t->dUtT.ensure(2 * 2 * S * P)) || (s = t->dBc.ensure(4 * 2 * S * t->p)) ||
+  if ((s = t->Bc.ensure(2 * 2 * S * t->p)) || (s = t->BcT.ensure(2 * 2 * S * t->p)) ||
       (s = t->part.ensure(4 * t->part_floats)) || (s = t->bpart.ensure(4 * t->part_floats)) || (s = t->lpart.ensure(8 * 2 * S * nch)) || (s = t->wv.ensure(4 * S)) ||
       (s = t->ctr.ensure(64)) || (s = t->losses.ensure(4 * (size_t)o->max_steps)) ||
       (s = t->idx.ensure(4 * (size_t)o->max_steps * S)))
@@ -1046,7 +1496,7 @@ helm_status don_train_create(don_net net, const don_train_opts* o, const double*
     e = hipMemcpy(tmp.ptr, fx.data(), sizeof(float) * fx.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
       hipLaunchKernelGGL(k_pad_rows, dim3(grid_for((long)P * Kt)), dim3(256), 0, t->st, (long)P, t->d,
-                         (const float*)tmp.ptr, (int)Kt, (__bf16*)t->X.ptr, (__bf16*)t->XT.ptr);
+                         (const float*)tmp.ptr, (int)Kt, (__bf16*)t->X.ptr, (__bf16*)nullptr);
     s = e == hipSuccess ? sync(t, "don_train_create") : hip_fail(e, "don_train_create: X");
     tmp.release();
     if (s) return fin(s);
