@@ -430,165 +430,274 @@ __global__ __launch_bounds__(1024) void k_chol_drop(int p, const double* __restr
 }
 
 // ---- Gauss-Jordan inverse of a complex r x r matrix (r <= 128), one workgroup ----
-// The matrix lives in registers: thread t owns row t / 8 and the 16 columns
-// [16 (t % 8), 16 (t % 8) + 16), rotated by one register after every pivot
-// (before pivot k, a[q] holds column 16 (t % 8) + ((q + k) & 15)), so that the
-// pivot column is always a[0] of the threads that own it and every register
-// index is static.  In-place Gauss-Jordan with partial pivoting
-// (largest modulus among the rows not yet used as pivot rows, lowest row on
-// ties), without moving rows: per pivot the column is published in LDS (and
-// zeroed in the registers), every wavefront picks the pivot row p from the
-// published moduli, row p is scaled and broadcast, and every other row is
-// updated.  Row p of the final table is then row k of the inverse where p was
-// column k's pivot row, and its column c is column p_c (the pivot row of
-// column c) of the inverse.  info[0] = 1 if a pivot was zero or non-finite;
-// cond[0] = ||A||_1 ||A^{-1}||_1.
-__global__ __launch_bounds__(1024) void k_gj_inverse(int r, const double* __restrict__ A, double* __restrict__ Ainv,
-                                                     int* __restrict__ info, double* __restrict__ cond) {
-  // prow holds the pivot row with one pad entry per 16 columns: the eight
-  // column blocks a wavefront reads at once then fall in different LDS banks
-  __shared__ double2 pcol[2][128], prow[128 + 8];
-  __shared__ double pabs[2][128], csum[128];
-  __shared__ double npart[8][128];
+// In-place Gauss-Jordan with partial pivoting (largest |Re| + |Im| among the rows
+// not yet used as pivot rows, lowest row on ties), without moving rows, eight
+// columns at a time.  A panel's eight steps touch only its own columns: wavefront 8
+// takes the 128 x 8 panel in registers (lane l rows l and l + 64), with no
+// barrier between pivots.  They leave in the panel the columns F_t = G
+// e_{p_t} of the transformation G of the eight steps (p_t: step t's pivot row);
+// every other column a becomes G a = a with its pivot rows zeroed + sum_t
+// a[p_t] F_t, a product of depth eight that wavefronts 0 .. 7 run on the matrix
+// pipe, the matrix in their accumulators (wavefront w: rows 16 w .. + 15, eight
+// 16 x 16 tiles, Re and Im).  They update the next panel's columns first, so its
+// pivots are found while the other columns are updated.  Row p of the final
+// table is row k of the inverse where p was column k's pivot row, and its column c
+// is column p_c (the pivot row of column c) of the inverse.  The matrix is padded
+// with the identity to whole blocks.  info[0] = 1 if a pivot was zero or
+// non-finite; cond[0] = ||A||_1 ||A^{-1}||_1.
+// What bounds it: the panels' chain of pivot searches, reciprocals and rank-one
+// updates in one wavefront; the products (55 us of one CU's fp64 rate at r = 128)
+// run beside it.  One pivot at a time over the whole matrix, two barriers and
+// 563 instructions each, took 378 us at r = 128 (118 at 48); this one
+// takes 187 us (55 at 48).
+constexpr int GJ_P = 8;
+__device__ __forceinline__ double lane_val(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_max(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return fmax(v, __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                                  __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false)));
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = dpp_max<0xB1>(dpp_max<0x4E>(dpp_max<0x141>(dpp_max<0x140>(v))));  // within the 16-lane rows
+  return fmax(fmax(lane_val(v, 0), lane_val(v, 16)), fmax(lane_val(v, 32), lane_val(v, 48)));
+}
+
+// 1 / z, scaled by the exponent of the larger part (no overflow of |z|^2)
+__device__ __forceinline__ double2 crcp(double2 z) {
+  const int k = -ilogb(fmax(fabs(z.x), fabs(z.y)));
+  const double x = ldexp(z.x, k), y = ldexp(z.y, k), d = x * x + y * y;  // d in [1, 8)
+  double v = __builtin_amdgcn_rcp(d);
+  v = fma(v, fma(-d, v, 1.0), v);
+  v = fma(v, fma(-d, v, 1.0), v);
+  return make_double2(ldexp(x * v, k), ldexp(-y * v, k));
+}
+
+__global__ __launch_bounds__(576) void k_gj_inverse(int r, const double* __restrict__ A, double* __restrict__ Ainv,
+                                                    int* __restrict__ info, double* __restrict__ cond) {
+  // panel kp (then its F), its pivot rows' entries in all columns, and each
+  // row's step in it (-1: none), alternating
+  __shared__ double2 pan[2][128][GJ_P + 1], prow[2][GJ_P][128 + 2];
+  __shared__ int rowt[2][128];
+  __shared__ double csum[128], npart[4][128];
   __shared__ int perm[128], rowof[128];
   __shared__ int s_bad;
-  const int t = threadIdx.x, lane = t & 63;
-  const int i = t >> 3, cb = t & 7, c0 = 16 * cb;
-  const bool row_in = i < r;
-  bool used = false;  // row i has been a pivot row
-  double2 a[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int c = c0 + q;
-    a[q] = (row_in && c < r) ? make_double2(A[2 * ((size_t)i * r + c)], A[2 * ((size_t)i * r + c) + 1]) : czero();
-  }
-  // column k (a[0] of its owners) into buffer k & 1 (entries, and the moduli
-  // of the rows not yet pivot rows), and zeroed in the registers: the update
-  // of column k then leaves -f / pivot there
-  auto publish = [&](int k) {
-    if (cb == (k >> 4)) {
-      const double2 v = a[0];
-      a[0] = czero();
-      if (row_in) {
-        pcol[k & 1][i] = v;
-        pabs[k & 1][i] = used ? -1.0 : hypot(v.x, v.y);
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int m = lane & 15, g = lane >> 4;
+  const int nb = (r + 15) / 16, np = 2 * nb;
+  // ||M||_1 partials: column t % 128 over rows t / 128 + 4 u (coalesced), later added in order
+  auto norm1 = [&](const double2* M) {
+    const int c = t & 127, r0 = t >> 7;
+    if (r0 > 3) return;
+    double sm = 0.0;
+    if (c < r)
+      for (int i = r0; i < r; i += 4) {
+        const double2 v = M[(size_t)i * r + c];
+        sm += hypot(v.x, v.y);
       }
-    }
+    npart[r0][c] = sm;
   };
-  publish(0);
-  // ||A||_1: column sums, column t % 128 over rows t / 128 + 8 u (coalesced), the
-  // eight partials added in order
-  {
-    const int c = t & 127, r0 = t >> 7;
-    double sm = 0.0;
-    if (c < r)
-      for (int ii = r0; ii < r; ii += 8) sm += hypot(A[2 * ((size_t)ii * r + c)], A[2 * ((size_t)ii * r + c) + 1]);
-    npart[r0][c] = sm;
-  }
+  norm1(reinterpret_cast<const double2*>(A));
   if (t == 0) s_bad = 0;
-  if (t < 128) rowof[t] = t;  // every row maps in range even if a failed pivot search repeats a row
-  __syncthreads();
   if (t < 128) {
-    double sm = 0.0;
-    for (int q = 0; q < 8; ++q) sm += npart[q][t];
-    csum[t] = sm;
-  }
-  // Per pivot: two barriers.  Every wavefront finds the pivot itself from the
-  // published moduli (same data, same order, same result), and the update for
-  // column k publishes column k + 1 into the other buffer.
-  for (int k = 0; k < r; ++k) {
-    const int buf = k & 1;
-    double best = -2.0;
-    int bi = 0;
-    for (int ii = lane; ii < r; ii += 64)
-      if (pabs[buf][ii] > best) {
-        best = pabs[buf][ii];
-        bi = ii;
-      }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const double ob = __shfl_xor(best, off, 64);
-      const int oi = __shfl_xor(bi, off, 64);
-      if (ob > best || (ob == best && oi < bi)) {
-        best = ob;
-        bi = oi;
-      }
-    }
-    const int p = bi;
-    if (t == 0) {
-      perm[k] = p;
-      rowof[p] = k;
-      if (!(best > 0.0) || !isfinite(best)) s_bad = 1;
-    }
-    // pivot row p: entry k <- 1, row *= 1 / pivot; publish it
-    if (i == p) {
-      used = true;
-      const double2 ipiv = cdiv(make_double2(1.0, 0.0), pcol[buf][p]);
-      const bool ownk = cb == (k >> 4);
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const double2 v = (q == 0 && ownk) ? make_double2(1.0, 0.0) : a[q];
-        a[q] = cmul(v, ipiv);
-        prow[c0 + q + cb] = a[q];  // slot (cb, q) holds the same column for every thread
-      }
-    }
-    __syncthreads();
-    // every other row: A[i][:] <- A[i][:] - f A[p][:] (A[i][k] is 0 here), two
-    // fused multiply-adds per component
-    if (i != p && row_in) {
-      const double2 f = pcol[buf][i];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const double2 pv = prow[c0 + q + cb];
-        a[q].x = fma(-f.x, pv.x, fma(f.y, pv.y, a[q].x));
-        a[q].y = fma(-f.x, pv.y, fma(-f.y, pv.x, a[q].y));
-      }
-    }
-    // rotate: a[q] <- a[q + 1], so a[0] holds column 16 cb + ((k + 1) & 15)
-    {
-      const double2 a0 = a[0];
-#pragma unroll
-      for (int q = 0; q < 15; ++q) a[q] = a[q + 1];
-      a[15] = a0;
-    }
-    if (k + 1 < r) publish(k + 1);
-    __syncthreads();
-  }
-  // row i of the table is row rowof[i] of the inverse; its column c is column
-  // perm[c]; after r rotations a[q] holds column 16 cb + ((q + r) & 15)
-  if (row_in) {
-    const int to_row = rowof[i];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int c = c0 + ((q + r) & 15);
-      if (c < r) {
-        const int to = perm[c];
-        Ainv[2 * ((size_t)to_row * r + to)] = a[q].x;
-        Ainv[2 * ((size_t)to_row * r + to) + 1] = a[q].y;
-      }
-    }
+    rowof[t] = t;  // every row maps in range even if a failed pivot search repeats a row
+    perm[t] = t;
   }
   __syncthreads();
-  {
-    const int c = t & 127, r0 = t >> 7;
-    double sm = 0.0;
-    if (c < r)
-      for (int ii = r0; ii < r; ii += 8)
-        sm += hypot(Ainv[2 * ((size_t)ii * r + c)], Ainv[2 * ((size_t)ii * r + c) + 1]);
-    npart[r0][c] = sm;
+  if (t < 128) csum[t] = (npart[0][t] + npart[1][t]) + (npart[2][t] + npart[3][t]);
+  if (w == 8) {
+    __syncthreads();  // panel 0 is laid out
+    bool used0 = lane >= 16 * nb, used1 = lane + 64 >= 16 * nb;
+    for (int kp = 0; kp < np; ++kp) {
+      double2(*pn)[GJ_P + 1] = pan[kp & 1];
+      double2 v0[GJ_P], v1[GJ_P];
+#pragma unroll
+      for (int c = 0; c < GJ_P; ++c) {
+        v0[c] = pn[lane][c];
+        v1[c] = pn[lane + 64][c];
+      }
+      int t0 = -1, t1 = -1;
+#pragma unroll
+      for (int c = 0; c < GJ_P; ++c) {
+        const double a0 = used0 ? -1.0 : fabs(v0[c].x) + fabs(v0[c].y);
+        const double a1 = used1 ? -1.0 : fabs(v1[c].x) + fabs(v1[c].y);
+        const double best = wave_max(fmax(a0, a1));
+        const unsigned long long b0 = __ballot(a0 == best), b1 = __ballot(a1 == best);
+        const int p = b0 ? __ffsll(b0) - 1 : b1 ? 63 + __ffsll(b1) : 0;
+        const int pl = p & 63;
+        // the pivot row (uniform) times 1 / pivot; every other row minus (its entry / pivot) times the pivot row
+        double2 pr[GJ_P], f0, f1, ipiv;
+        if (p < 64) {
+#pragma unroll
+          for (int j = 0; j < GJ_P; ++j) pr[j] = make_double2(lane_val(v0[j].x, pl), lane_val(v0[j].y, pl));
+          ipiv = crcp(pr[c]);
+          f0 = cmul(v0[c], ipiv);
+          f1 = cmul(v1[c], ipiv);
+          if (lane == pl) {
+            used0 = true;
+            t0 = c;
+            f0 = make_double2(-ipiv.x, -ipiv.y);
+#pragma unroll
+            for (int j = 0; j < GJ_P; ++j) v0[j] = czero();
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < GJ_P; ++j) pr[j] = make_double2(lane_val(v1[j].x, pl), lane_val(v1[j].y, pl));
+          ipiv = crcp(pr[c]);
+          f0 = cmul(v0[c], ipiv);
+          f1 = cmul(v1[c], ipiv);
+          if (lane == pl) {
+            used1 = true;
+            t1 = c;
+            f1 = make_double2(-ipiv.x, -ipiv.y);
+#pragma unroll
+            for (int j = 0; j < GJ_P; ++j) v1[j] = czero();
+          }
+        }
+        pr[c] = make_double2(1.0, 0.0);
+        v0[c] = v1[c] = czero();
+#pragma unroll
+        for (int j = 0; j < GJ_P; ++j) {
+          v0[j].x = fma(-f0.x, pr[j].x, fma(f0.y, pr[j].y, v0[j].x));
+          v0[j].y = fma(-f0.x, pr[j].y, fma(-f0.y, pr[j].x, v0[j].y));
+          v1[j].x = fma(-f1.x, pr[j].x, fma(f1.y, pr[j].y, v1[j].x));
+          v1[j].y = fma(-f1.x, pr[j].y, fma(-f1.y, pr[j].x, v1[j].y));
+        }
+        if (lane == 0) {
+          perm[GJ_P * kp + c] = p;
+          rowof[p] = GJ_P * kp + c;
+          if (!(best > 0.0) || !isfinite(best)) s_bad = 1;
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < GJ_P; ++c) {
+        pn[lane][c] = v0[c];
+        pn[lane + 64][c] = v1[c];
+      }
+      rowt[kp & 1][lane] = t0;
+      rowt[kp & 1][lane + 64] = t1;
+      __syncthreads();  // F is there
+      __syncthreads();  // its pivot rows are published
+      __syncthreads();  // the next panel is laid out
+    }
+  } else {
+    const bool on = w < nb;
+    const double2* A2 = reinterpret_cast<const double2*>(A);
+    // tile q holds column block (q + rot) & 7: the tiles move down one place after
+    // each two panels, so the panel's own tile is tile 0 and no index is dynamic
+    d4 re[8], im[8];
+    int rot = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = 16 * w + acc_row(lane, i), col = 16 * q + m;
+        const double2 v = row < r && col < r ? A2[(size_t)row * r + col] : make_double2(row == col ? 1.0 : 0.0, 0.0);
+        re[q][i] = v.x;
+        im[q][i] = v.y;
+      }
+    // half h of tile q as a panel
+    auto lay_out = [&](int h, const d4& x, const d4& y) {
+      if (on && (m >> 3) == h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pan[h][16 * w + acc_row(lane, i)][m & 7] = make_double2(x[i], y[i]);
+    };
+    lay_out(0, re[0], im[0]);
+    __syncthreads();
+    for (int kp = 0; kp < np; kp += 2) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        __syncthreads();  // F of panel kp + h
+        if (on)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int tt = rowt[h][16 * w + acc_row(lane, i)];
+            if (tt >= 0)
+#pragma unroll
+              for (int q = 0; q < 8; ++q) {
+                prow[h][tt][16 * ((q + rot) & 7) + m] = make_double2(re[q][i], im[q][i]);
+                re[q][i] = im[q][i] = 0.0;
+              }
+          }
+        __syncthreads();  // the pivot rows
+        double2 f[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) f[s] = pan[h][16 * w + m][g + 4 * s];
+        auto update = [&](int cb, d4& x, d4& y) {
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const double2 v = prow[h][g + 4 * s][16 * cb + m];
+            x = mfma16(f[s].x, v.x, x);
+            y = mfma16(f[s].x, v.y, y);
+            x = mfma16(-f[s].y, v.y, x);
+            y = mfma16(f[s].y, v.x, y);
+          }
+        };
+        auto own = [&]() {  // the panel's own columns are F
+          update(rot, re[0], im[0]);
+          if ((m >> 3) == h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const double2 v = pan[h][16 * w + acc_row(lane, i)][m & 7];
+              re[0][i] = v.x;
+              im[0][i] = v.y;
+            }
+        };
+        if (on) {
+          if (h == 0) {
+            own();
+            lay_out(1, re[0], im[0]);
+          } else if (rot + 1 < nb) {
+            update(rot + 1, re[1], im[1]);
+            lay_out(0, re[1], im[1]);
+          }
+        }
+        __syncthreads();  // panel kp + h + 1
+        if (on) {
+          if (h == 1) own();
+#pragma unroll
+          for (int q = 1; q < 8; ++q) {
+            const int cb = (q + rot) & 7;
+            if (cb < nb && (h == 0 || q > 1 || cb == 0)) update(cb, re[q], im[q]);
+          }
+        }
+      }
+      const d4 x = re[0], y = im[0];
+#pragma unroll
+      for (int q = 0; q < 7; ++q) {
+        re[q] = re[q + 1];
+        im[q] = im[q + 1];
+      }
+      re[7] = x;
+      im[7] = y;
+      ++rot;
+    }
+    // row i of the table is row rowof[i] of the inverse; its column c is column perm[c] (rot == nb)
+    double2* I2 = reinterpret_cast<double2*>(Ainv);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = 16 * w + acc_row(lane, i), col = 16 * ((q + rot) & 7) + m;
+        if (row < r && col < r) {
+          const int tr = rowof[row], tc = perm[col];
+          if (tr < r && tc < r) I2[(size_t)tr * r + tc] = make_double2(re[q][i], im[q][i]);
+        }
+      }
   }
   __syncthreads();
-  if (t < 128) {
-    double sm = 0.0;
-    for (int q = 0; q < 8; ++q) sm += npart[q][t];
-    pabs[0][t] = sm;
-  }
+  norm1(reinterpret_cast<const double2*>(Ainv));
+  __syncthreads();
+  if (t < 128) npart[0][t] = (npart[0][t] + npart[1][t]) + (npart[2][t] + npart[3][t]);
   __syncthreads();
   if (t == 0) {
     double na = 0.0, ni = 0.0;
     for (int c = 0; c < r; ++c) {
       na = fmax(na, csum[c]);
-      ni = fmax(ni, pabs[0][c]);
+      ni = fmax(ni, npart[0][c]);
     }
     cond[0] = na * ni;
     info[0] = s_bad;
@@ -685,7 +794,7 @@ void chol_drop(int p, double* G, double tau2, int allow_drop, double* X, double*
 
 void gj_inverse(int r, const double* A, double* work, double* Ainv, int* info, double* cond, hipStream_t st) {
   (void)work;
-  hipLaunchKernelGGL(k_gj_inverse, dim3(1), dim3(1024), 0, st, r, A, Ainv, info, cond);
+  hipLaunchKernelGGL(k_gj_inverse, dim3(1), dim3(576), 0, st, r, A, Ainv, info, cond);
 }
 
 template void coord_layer<double>(int, const int*, size_t, size_t, const double*, const double*, int, int, double*,
