@@ -17,40 +17,41 @@ __device__ __forceinline__ d4 mfma16(double a, double b, d4 c) {
 }
 __device__ __forceinline__ int acc_row(int lane, int i) { return (lane >> 4) + 4 * i; }
 
-// tanh for the fp64 layers from expm1: t = e^{2|x|} - 1, tanh|x| = t / (t + 2),
-// sign restored (no cancellation near 0).  2|x| = n ln 2 + r with |r| <= ln 2 / 2,
-// e^r - 1 by its Taylor series to r^13 (the rest is below 2e-17 r), then
-// t = 2^n (e^r - 1) + (2^n - 1), exact in its second term; the quotient by
-// Newton's iteration on the reciprocal of t + 2 in [2, 2^64] and one correction.
-// About 35 fp64 instructions, where the library expm1 and a general division
-// take about 60: the vector fp64 work shares its units with the fp64 matrix
-// products, so it adds to their time.  Past 2|x| = 44 the result is 1; NaN
-// stays NaN.
+// tanh for the fp64 layers from expm1: with t = (e^{2|x|} - 1) / 2, tanh|x| = t / (t + 1),
+// sign restored (no cancellation near 0).  |x| = n ln 2 / 2 + r with |r| <= ln 2 / 4,
+// (e^{2r} - 1) / 2 = r + r^2 q(r), q the degree-10 interpolant at the Chebyshev
+// nodes of the range (error 8e-19 of the value), then t = 2^n (r + r^2 q) +
+// (2^n - 1) / 2, exact in its second term; n and 2^n without conversions, from the
+// low word of |x| 2 / ln 2 + 1.5 * 2^52; the quotient by one third-order step on the
+// reciprocal of t + 1 in [1, 2^63] and one correction.  27 fp64 instructions, where
+// the library expm1 and a general division take about 60: fp64 work adds to the
+// time of the matrix products beside it.  Past |x| = 22 the result is 1; NaN
+// stays NaN unless the caller rules it out (NANS).
+template <bool NANS = true>
 __device__ __forceinline__ double tanh_fast(double x) {
-  const double ax = 2.0 * fabs(x);
-  const double y = ax > 44.0 ? 44.0 : ax;
-  const double n = rint(y * 1.4426950408889634);
-  double r = fma(n, -0.6931471805599453, y);
-  r = fma(n, -2.3190468138462996e-17, r);
-  double q = 1.0 / 6227020800.0;
-  q = fma(q, r, 1.0 / 479001600.0);
-  q = fma(q, r, 1.0 / 39916800.0);
-  q = fma(q, r, 1.0 / 3628800.0);
-  q = fma(q, r, 1.0 / 362880.0);
-  q = fma(q, r, 1.0 / 40320.0);
-  q = fma(q, r, 1.0 / 5040.0);
-  q = fma(q, r, 1.0 / 720.0);
-  q = fma(q, r, 1.0 / 120.0);
-  q = fma(q, r, 1.0 / 24.0);
-  q = fma(q, r, 1.0 / 6.0);
-  q = fma(q, r, 0.5);
+  const double ax = fabs(x);
+  const double y = NANS ? (ax > 22.0 ? 22.0 : ax) : fmin(ax, 22.0);
+  const double m = fma(y, 2.8853900817779268, 6755399441055744.0), n = m - 6755399441055744.0;
+  double r = fma(n, -0.34657359027997264, y);
+  r = fma(n, -1.1600963245594897e-17, r);
+  double q = 4.283334771688116e-06;
+  q = fma(q, r, 2.5707771489828415e-05);
+  q = fma(q, r, 0.00014109323851772937);
+  q = fma(q, r, 0.0007054657366917812);
+  q = fma(q, r, 0.0031746031778077236);
+  q = fma(q, r, 0.012698412719909201);
+  q = fma(q, r, 0.044444444444425406);
+  q = fma(q, r, 0.13333333333321806);
+  q = fma(q, r, 0.33333333333333337);
+  q = fma(q, r, 0.6666666666666669);
+  q = fma(q, r, 1.0);
   const double p = fma(r * r, q, r);
-  const double s = __hiloint2double(((int)n + 1023) << 20, 0);
-  const double t = fma(s, p, s - 1.0);
-  const double d = t + 2.0;
+  const double s = __hiloint2double((__double2loint(m) << 20) + 0x3FF00000, 0);
+  const double t = fma(s, p, fma(s, 0.5, -0.5));
+  const double d = t + 1.0;
   double v = __builtin_amdgcn_rcp(d);
-  v = fma(v, fma(-d, v, 1.0), v);
-  v = fma(v, fma(-d, v, 1.0), v);
+  const double e = fma(-d, v, 1.0);
+  v = fma(v, fma(e, e, e), v);
   const double u = t * v;
   return copysign(fma(v, fma(-d, u, t), u), x);
 }
