@@ -16,7 +16,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libhelm.so")
-SOURCES = ["stencil.hip", "relax.hip", "blas1.hip", "gmres.hip", "dense.hip", "trunk.hip", "coarse.hip", "deeponet.hip", "meta.hip", "prof.hip",
+SOURCES = ["stencil.hip", "relax.hip", "blas1.hip", "gmres.hip", "dense.hip", "trunk.hip", "gram.hip", "coarse.hip", "deeponet.hip", "meta.hip", "prof.hip",
            "adjoint.hip", "batch.hip", "train.hip", "mg.hip", "noalloc.hip", "pool.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

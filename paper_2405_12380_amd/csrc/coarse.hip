@@ -151,12 +151,6 @@ __global__ __launch_bounds__(256) void k_batched_lap(StencilGeom g, int r, const
   }
 }
 
-template <typename S>
-__global__ void k_im_s(size_t n, const cplx_t<S>* __restrict__ sc, double* __restrict__ w) {
-  for (size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x; p < n; p += (size_t)gridDim.x * blockDim.x)
-    w[p] = ldc(sc, p).y;
-}
-
 // P = T[:, :pu] (T: n x p, dtype precision) in fp64 with masked rows zeroed
 template <typename T>
 __global__ void k_mask_cols(size_t n, int p, int pu, const T* __restrict__ Tm, const uint8_t* __restrict__ mask,
@@ -189,15 +183,6 @@ __global__ void k_round_q(size_t total, double* __restrict__ Q, T* __restrict__ 
     const T v = (T)Q[e];
     Qs[e] = v;
     Q[e] = (double)v;
-  }
-}
-
-__global__ void k_combine_ac(int r2, const double* __restrict__ re, const double* __restrict__ im,
-                             double* __restrict__ Ac) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < r2) {
-    Ac[2 * e] = re[e];
-    Ac[2 * e + 1] = -im[e];
   }
 }
 
@@ -393,16 +378,14 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
   c.pass1 = !c.q_f32;  // fp64 basis: the first pass's basis is the one used
   if (!wide_t && (s = c.W1.ensure(n * (size_t)pu * sizeof(double)))) return s;
   if (c.q_f32 && (s = c.W2.ensure(n * (size_t)pu * sizeof(double)))) return s;
-  const size_t small_doubles = (size_t)gram_nblocks(n) * pu * pu + 10 * (size_t)pu * pu + 4096;
+  const size_t small_doubles = gram_part(n, pu) + 8 * (size_t)pu * pu + 4096;
   if ((s = c.small.ensure(small_doubles * sizeof(double)))) return s;
   double* part = (double*)c.small.ptr;
-  double* G = part + (size_t)gram_nblocks(n) * pu * pu;
+  double* G = part + gram_part(n, pu);
   double* X = G + (size_t)pu * pu;
   double* S1 = X + (size_t)pu * pu;
   double* G2 = S1 + (size_t)pu * pu;
-  double* are = G2 + (size_t)pu * pu;
-  double* aim = are + (size_t)pu * pu;
-  double* gjw = aim + (size_t)pu * pu;  // 4 pu^2
+  double* gjw = G2 + (size_t)pu * pu;  // 4 pu^2
   int* info = (int*)(gjw + 4 * (size_t)pu * pu);
   double* cond = (double*)(info + 8);
   double* Q1 = (double*)c.W2.ptr;
@@ -422,7 +405,7 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
     ldp = (size_t)pu;
   }
   // pass 1: G = P^T P, Cholesky with dropping -> S1 (pu x r)
-  gram(n, pu, P, ldp, P, ldp, nullptr, part, G, st);
+  gram(n, pu, P, ldp, part, G, st);
   const double tau = op->dt == HELM_C128 ? 1e-7 : 1e-5;
   chol_drop(pu, G, tau * tau, 1, X, S1, info, st);
   hipError_t e = hipMemcpyAsync(op->host, info, 2 * sizeof(int), hipMemcpyDeviceToHost, st);
@@ -444,17 +427,13 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
       (s = c.qpart.ensure(sizeof(double) * 2 * (size_t)r * qt_nblocks(n, r, c.q_f32 ? sizeof(float) : sizeof(double)))))
     return s;
   // the Galerkin matrix X^T A X = X^T B - i X^T diag(Im s) X of an n x r basis
-  // X into out (complex r x r); B = (L - diag(Re s)) X and then Im s go
-  // through the n x r buffer B
+  // X into out (complex r x r), B = (L - diag(Re s)) X
   auto galerkin = [&](const double* X, double* B, double* out) {
     size_t nbl = (n + 3) / 4;
     if (nbl > 16384) nbl = 16384;
     hipLaunchKernelGGL((k_batched_lap<S>), dim3((unsigned)nbl), dim3(64, 4), 0, st, op->geom, r, X,
                        (const cplx_t<S>*)op->sc, op->code, B);
-    gram(n, r, X, r, B, r, nullptr, part, are, st);
-    hipLaunchKernelGGL((k_im_s<S>), dim3(ew_grid(n)), dim3(256), 0, st, n, (const cplx_t<S>*)op->sc, B);
-    gram(n, r, X, r, X, r, B, part, aim, st);
-    hipLaunchKernelGGL(k_combine_ac, dim3((r * r + 255) / 256), dim3(256), 0, st, r * r, are, aim, out);
+    gram_galerkin<S>(n, r, X, B, (const cplx_t<S>*)op->sc, part, out, st);
   };
   double* Ac = (double*)c.Ac.ptr;
   if (c.pass1) {
@@ -472,7 +451,7 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
     // record goes to info[2..3], read back with the inverse's record (every
     // kernel below is sized by r alone, so a lost rank only spoils values).
     gemm<double>((int)n, r, pu, P, ldp, S1, r, nullptr, ACT_NONE, Q1, r, st);
-    gram(n, r, Q1, r, Q1, r, nullptr, part, G2, st);
+    gram(n, r, Q1, r, part, G2, st);
     chol_drop(r, G2, 0.0, 0, X, S1, info + 2, st);
     double* Q = (double*)c.W1.ptr;
     gemm<double>((int)n, r, r, Q1, r, S1, r, nullptr, ACT_NONE, Q, r, st);
@@ -525,15 +504,15 @@ helm_status coarse_orthonormal(helm_op_s* op, double* Qout, double* Acout, hipSt
   if (r == 0) return HELM_OK;
   // the regions of the set-up's small buffer (laid out as in coarse_build)
   double* part = (double*)c.small.ptr;
-  double* G = part + (size_t)gram_nblocks(n) * pu * pu;
+  double* G = part + gram_part(n, pu);
   double* X = G + (size_t)pu * pu;
   double* S2 = X + (size_t)pu * pu;
   double* G2 = S2 + (size_t)pu * pu;
-  double* gjw = G2 + 3 * (size_t)pu * pu;
+  double* gjw = G2 + (size_t)pu * pu;
   int* info = (int*)(gjw + 4 * (size_t)pu * pu);
   const double* Q1 = (const double*)c.Q.ptr;
   // second CholeskyQR pass: G2 = Q1^T Q1 = S2^-T S2^-1
-  gram(n, r, Q1, r, Q1, r, nullptr, part, G2, st);
+  gram(n, r, Q1, r, part, G2, st);
   chol_drop(r, G2, 0.0, 0, X, S2, info + 2, st);
   if (Qout) gemm<double>((int)n, r, r, Q1, r, S2, r, nullptr, ACT_NONE, Qout, r, st);
   hipError_t e;

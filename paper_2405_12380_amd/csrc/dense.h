@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include "common.h"
+
 namespace helm {
 
 enum { ACT_NONE = -1, ACT_TANH = 0, ACT_RELU = 1, ACT_LEAKY = 2 };
@@ -43,12 +45,14 @@ int small_ksplit(int K);
 template <typename T>
 void dense_small(int B, int N, int K, const T* x, const T* W, const T* bias, int act, T* y, double* part,
                  hipStream_t st);
-// out (r x r) = X^T diag(w) Y for X, Y of n rows (row strides ldx, ldy), r <= 128;
-// part needs gram_nblocks(n) * r * r doubles; w may be NULL
-int gram_nblocks(size_t n);
-void gram(size_t n, int r, const double* X, size_t ldx, const double* Y, size_t ldy, const double* w, double* part,
-          double* out, hipStream_t st);
-void reduce_rows(const double* part, int nparts, size_t width, double* out, double scale, hipStream_t st);
+// out (r x r) = X^T X for X of n rows (row stride ldx), r <= 128; part: gram_part(n, r) doubles
+size_t gram_part(size_t n, int r);
+void gram(size_t n, int r, const double* X, size_t ldx, double* part, double* out, hipStream_t st);
+// Ac (complex r x r) = X^T B - i X^T diag(Im s) X, both products symmetric (X, B:
+// n x r; s: n complex values; instantiated for double and float)
+template <typename S>
+void gram_galerkin(size_t n, int r, const double* X, const double* B, const cplx_t<S>* s, double* part, double* Ac,
+                   hipStream_t st);
 // Cholesky with dropping of columns whose remaining squared norm is <= tau2 times
 // the largest squared column norm; G (p x p) is overwritten; X: p*p scratch;
 // S: p*p output capacity; info: 2 ints (rank, failed)

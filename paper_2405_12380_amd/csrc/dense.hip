@@ -1,7 +1,6 @@
 // Dense kernels: the DeepONet layers (MFMA GEMM with fused bias + activation,
 // split-K GEMV for small batches, the coordinate input layer of the trunk),
-// the tall-skinny Gram products of the trunk-basis setup (MFMA), and
-// one-workgroup factorizations of small matrices (Cholesky with column
+// and one-workgroup factorizations of small matrices (Cholesky with column
 // dropping, triangular inverse, Gauss-Jordan inverse of the complex coarse
 // matrix).
 // Both dtypes evaluate the network layers in fp64 (a C64 network's fp32
@@ -176,100 +175,6 @@ __global__ void k_small_final(int B, int N, int ksplit, const double* __restrict
   for (int ks = 0; ks < ksplit; ++ks) acc += part[((size_t)ks * B + b) * N + n];
   if (bias) acc += (double)bias[n];
   y[e] = (T)activate<double>(acc, act);  // fp64 arithmetic, rounded once to the stored type
-}
-
-// ---- tall-skinny weighted Gram: C = X^T diag(w) Y (X, Y: n x r, r <= 128) -------
-// Each workgroup reduces a contiguous range of rows into a full 128 x 128 tile
-// (four wavefronts of 64 x 64, 4 x 4 MFMA tiles each); rows are staged 16 at a
-// time through LDS.  part[b] receives the block's r x r partial.  MODE:
-// GRAM_XY (X^T Y), GRAM_XWY (X^T diag(w) Y), GRAM_XX (X^T X: Y is X and is
-// neither loaded nor staged a second time), GRAM_XWX (X^T diag(w) X: X staged
-// once, the weights applied to the second operand as it is read from LDS).
-constexpr int GR_ROWS = 16;
-enum { GRAM_XY = 0, GRAM_XWY = 1, GRAM_XX = 2, GRAM_XWX = 3 };
-template <int MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gram(size_t n, int r,
-                                              const double* __restrict__ X, size_t ldx,
-                                              const double* __restrict__ Y, size_t ldy,
-                                              const double* __restrict__ w, size_t rows_per_block,
-                                              double* __restrict__ part) {
-  constexpr bool SYM = MODE == GRAM_XX || MODE == GRAM_XWX, SW = MODE == GRAM_XWX;
-  __shared__ double Xs[GR_ROWS][128 + 1];
-  __shared__ double Ys[SYM ? 1 : GR_ROWS][128 + 1];
-  __shared__ double ws[GR_ROWS];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int wa = (wave >> 1) * 64, wb = (wave & 1) * 64;
-  const size_t i0 = (size_t)blockIdx.x * rows_per_block;
-  const size_t i1 = min(n, i0 + rows_per_block);
-  d4 acc[4][4];
-  for (int a = 0; a < 4; ++a)
-    for (int b = 0; b < 4; ++b) acc[a][b] = d4{0, 0, 0, 0};
-  // 16 rows x 128 columns of X (and Y) per chunk; the next chunk's loads are in
-  // flight while the current one is multiplied
-  constexpr int NQ = GR_ROWS * 128 / 256;
-  double xv[NQ], yv[SYM ? 1 : NQ], wv = 0.0;
-  auto load = [&](size_t ib) {
-    if (SW && t < GR_ROWS) wv = ib + t < i1 ? w[ib + t] : 0.0;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int e = t + 256 * q, rr = e >> 7, cc = e & 127;
-      const size_t gi = ib + rr;
-      const bool in = gi < i1 && cc < r;
-      xv[q] = in ? X[gi * ldx + cc] : 0.0;
-      if (!SYM) {
-        yv[q] = in ? Y[gi * ldy + cc] : 0.0;
-        if (MODE == GRAM_XWY && in) yv[q] *= w[gi];
-      }
-    }
-  };
-  if (i0 < i1) load(i0);
-  for (size_t ib = i0; ib < i1; ib += GR_ROWS) {
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int e = t + 256 * q, rr = e >> 7, cc = e & 127;
-      Xs[rr][cc] = xv[q];
-      if (!SYM) Ys[rr][cc] = yv[q];
-    }
-    if (SW && t < GR_ROWS) ws[t] = wv;
-    __syncthreads();
-    if (ib + GR_ROWS < i1) load(ib + GR_ROWS);
-#pragma unroll
-    for (int kk = 0; kk < GR_ROWS; kk += 4) {
-      double av[4], bv[4];
-      for (int a = 0; a < 4; ++a) av[a] = Xs[kk + (lane >> 4)][wa + a * 16 + (lane & 15)];
-      for (int b = 0; b < 4; ++b)
-        bv[b] = SYM ? Xs[kk + (lane >> 4)][wb + b * 16 + (lane & 15)] : Ys[kk + (lane >> 4)][wb + b * 16 + (lane & 15)];
-      if (SW)
-        for (int b = 0; b < 4; ++b) bv[b] *= ws[kk + (lane >> 4)];
-      for (int a = 0; a < 4; ++a)
-        for (int b = 0; b < 4; ++b) acc[a][b] = mfma16(av[a], bv[b], acc[a][b]);
-    }
-    __syncthreads();
-  }
-  double* out = part + (size_t)blockIdx.x * r * r;
-  for (int a = 0; a < 4; ++a)
-    for (int b = 0; b < 4; ++b)
-      for (int i = 0; i < 4; ++i) {
-        const int ra = wa + a * 16 + acc_row(lane, i);
-        const int cb = wb + b * 16 + (lane & 15);
-        if (ra < r && cb < r) out[(size_t)ra * r + cb] = acc[a][b][i];
-      }
-}
-
-// out[w] = sum_b part[b * width + w] in block order (one thread per w).
-__global__ void k_reduce_rows(const double* __restrict__ part, int nparts, size_t width, double* __restrict__ out,
-                              double scale) {
-  const size_t w = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (w >= width) return;
-  double acc = 0.0;
-  for (int b0 = 0; b0 < nparts; b0 += 8) {  // eight partials' loads in flight, added in order
-    double v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = b0 + u < nparts ? part[(size_t)(b0 + u) * width + w] : 0.0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) acc += v[u];
-  }
-  out[w] = scale * acc;
 }
 
 // ---- one-workgroup Cholesky with column dropping -------------------------------
@@ -745,39 +650,6 @@ void dense_small(int B, int N, int K, const T* x, const T* W, const T* bias, int
   const int ncb = (N + SK_COLS - 1) / SK_COLS;
   hipLaunchKernelGGL((k_small_part<T>), dim3(ncb * ks), dim3(256), 0, st, B, N, K, ks, x, W, part);
   hipLaunchKernelGGL((k_small_final<T>), dim3((B * N + 255) / 256), dim3(256), 0, st, B, N, ks, part, bias, act, y);
-}
-
-int gram_nblocks(size_t n) {
-  // two workgroups per CU (the MFMA pipe needs two wavefronts per SIMD)
-  size_t nb = (n + 511) / 512;
-  if (nb > 512) nb = 512;
-  if (nb < 1) nb = 1;
-  return (int)nb;
-}
-
-void gram(size_t n, int r, const double* X, size_t ldx, const double* Y, size_t ldy, const double* w, double* part,
-          double* out, hipStream_t st) {
-  const int nb = gram_nblocks(n);
-  size_t rpb = (n + nb - 1) / nb;
-  rpb = (rpb + GR_ROWS - 1) / GR_ROWS * GR_ROWS;
-  kprof_begin(KP_MFMA, st);
-  if (w && X == Y && ldx == ldy)
-    hipLaunchKernelGGL(k_gram<GRAM_XWX>, dim3(nb), dim3(256), 0, st, n, r, X, ldx, Y, ldy, w, rpb, part);
-  else if (w)
-    hipLaunchKernelGGL(k_gram<GRAM_XWY>, dim3(nb), dim3(256), 0, st, n, r, X, ldx, Y, ldy, w, rpb, part);
-  else if (X == Y && ldx == ldy)
-    hipLaunchKernelGGL(k_gram<GRAM_XX>, dim3(nb), dim3(256), 0, st, n, r, X, ldx, Y, ldy, w, rpb, part);
-  else
-    hipLaunchKernelGGL(k_gram<GRAM_XY>, dim3(nb), dim3(256), 0, st, n, r, X, ldx, Y, ldy, w, rpb, part);
-  kprof_end(KP_MFMA, 2.0 * (double)n * r * r, st);
-  const size_t width = (size_t)r * r;
-  hipLaunchKernelGGL(k_reduce_rows, dim3((unsigned)((width + 255) / 256)), dim3(256), 0, st, part, nb, width, out,
-                     1.0);
-}
-
-void reduce_rows(const double* part, int nparts, size_t width, double* out, double scale, hipStream_t st) {
-  hipLaunchKernelGGL(k_reduce_rows, dim3((unsigned)((width + 255) / 256)), dim3(256), 0, st, part, nparts, width, out,
-                     scale);
 }
 
 void chol_drop(int p, double* G, double tau2, int allow_drop, double* X, double* S, int* info, hipStream_t st) {
