@@ -115,38 +115,50 @@ __global__ __launch_bounds__(256) void k_skinny(size_t n, int r, const T* __rest
 }
 
 // B = (L - diag(Re s)) Q on real columns (n x r, row-major); masked rows -> 0.
-// A row of 4 nodes per workgroup step (threadIdx.y), the 64 lanes across the
-// node's columns; absent neighbours (ghost or masked) come from the node's
-// neighbour code, so no coordinates are formed.
-template <typename S>
-__global__ __launch_bounds__(256) void k_batched_lap(StencilGeom g, int r, const double* __restrict__ Q,
+// A wavefront takes an (x, y) column of nodes and marches along a segment of z, its
+// lanes V columns of Q each: z neighbours pass through registers, and each XCD gets
+// one range of (x, y), so the x and y neighbours' rows are read while they lie in
+// its L2.  Absent neighbours (ghost or masked) come from the node's neighbour code;
+// an absent one reads the node itself, so that a node's loads are issued together.
+// Bound by reading Q and writing B (104 us at 64^3 x 128 at 5.15 TB/s).  A node at
+// a time over all XCDs, 8-byte loads behind seven branches took 217 us (every row
+// fetched for each of its three planes), node ranges by XCD 206, this 173 (89 -> 57
+// at 56 x 48 x 52 x 96, 376 -> 281 at 80 x 72 x 76 x 128).
+template <typename S, int V>
+__global__ __launch_bounds__(256) void k_batched_lap(StencilGeom g, int r, int seg, const double* __restrict__ Q,
                                                      const cplx_t<S>* __restrict__ sc, const uint8_t* __restrict__ code,
                                                      double* __restrict__ B) {
-  const size_t n = (size_t)g.nx * g.ny * g.nz;
-  const size_t ry = (size_t)g.nx * r, rz = (size_t)g.nx * g.ny * r;
-  for (size_t p = blockIdx.x * (size_t)blockDim.y + threadIdx.y; p < n; p += (size_t)gridDim.x * blockDim.y) {
-    const unsigned cd = code[p];
-    const size_t row = p * r;
-    const double sre = ldc(sc, p).x;
-    for (int j = threadIdx.x; j < r; j += 64) {
-      const size_t e = row + j;
-      if (cd & NB_SELF) {
-        B[e] = 0.0;
-        continue;
-      }
-      const double c = Q[e];
-      const double xm = (cd & NB_XM) ? 0.0 : Q[e - r];
-      const double xp = (cd & NB_XP) ? 0.0 : Q[e + r];
-      const double ym = (cd & NB_YM) ? 0.0 : Q[e - ry];
-      const double yp = (cd & NB_YP) ? 0.0 : Q[e + ry];
-      double acc = ((c - xm) + (c - xp)) * g.ih2[0];
+  typedef double dv __attribute__((ext_vector_type(V)));
+  const size_t nxy = (size_t)g.nx * g.ny, ry = (size_t)g.nx * r, rz = nxy * r;
+  // logical wavefront: segment fastest
+  const unsigned nseg = (g.nz + seg - 1) / seg;
+  const size_t lw = (size_t)xcd_remap(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const size_t q = lw / nseg;
+  if (q >= nxy) return;
+  const int z0 = (int)(lw % nseg) * seg, z1 = min(g.nz, z0 + seg);
+  auto at = [&](size_t e) { return *reinterpret_cast<const dv*>(Q + e); };
+  for (int j = threadIdx.x * V; j < r; j += 64 * V) {
+    size_t p = q + z0 * nxy;
+    dv c = at(p * r + j), zm = z0 > 0 ? at((p - nxy) * r + j) : dv(0.0);
+    for (int z = z0; z < z1; ++z, p += nxy) {
+      const size_t e = p * r + j;
+      const unsigned cd = __builtin_amdgcn_readfirstlane((unsigned)code[p]);
+      const double sre = ldc(sc, p).x;
+      dv xm = at(e - ((cd & NB_XM) ? 0 : r)), xp = at(e + ((cd & NB_XP) ? 0 : r));
+      dv ym = at(e - ((cd & NB_YM) ? 0 : ry)), yp = at(e + ((cd & NB_YP) ? 0 : ry));
+      const dv zn = at(e + (z + 1 < g.nz ? rz : 0));
+      if (cd & NB_XM) xm = dv(0.0);
+      if (cd & NB_XP) xp = dv(0.0);
+      if (cd & NB_YM) ym = dv(0.0);
+      if (cd & NB_YP) yp = dv(0.0);
+      dv acc = ((c - xm) + (c - xp)) * g.ih2[0];
       acc = acc + ((c - ym) + (c - yp)) * g.ih2[1];
-      if (g.dim == 3) {
-        const double zm = (cd & NB_ZM) ? 0.0 : Q[e - rz];
-        const double zp = (cd & NB_ZP) ? 0.0 : Q[e + rz];
-        acc = acc + ((c - zm) + (c - zp)) * g.ih2[2];
-      }
-      B[e] = acc - sre * c;
+      if (g.dim == 3)
+        acc = acc + ((c - ((cd & NB_ZM) ? dv(0.0) : zm)) + (c - ((cd & NB_ZP) ? dv(0.0) : zn))) * g.ih2[2];
+      acc = acc - sre * c;
+      __builtin_nontemporal_store((cd & NB_SELF) ? dv(0.0) : acc, reinterpret_cast<dv*>(B + e));
+      zm = c;
+      c = zn;
     }
   }
 }
@@ -429,9 +441,12 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
   // the Galerkin matrix X^T A X = X^T B - i X^T diag(Im s) X of an n x r basis
   // X into out (complex r x r), B = (L - diag(Re s)) X
   auto galerkin = [&](const double* X, double* B, double* out) {
-    size_t nbl = (n + 3) / 4;
-    if (nbl > 16384) nbl = 16384;
-    hipLaunchKernelGGL((k_batched_lap<S>), dim3((unsigned)nbl), dim3(64, 4), 0, st, op->geom, r, X,
+    auto lap = r % 2 ? k_batched_lap<S, 1> : k_batched_lap<S, 2>;  // rows of an odd length are not 16-byte aligned
+    // eight wavefronts per SIMD, if need be by shorter marches
+    const size_t nxy = n / op->geom.nz, want = (8192 + nxy - 1) / nxy;
+    const int seg = std::max(1, (int)(op->geom.nz / want));
+    const size_t waves = nxy * ((op->geom.nz + seg - 1) / seg);
+    hipLaunchKernelGGL(lap, dim3((unsigned)((waves + 3) / 4)), dim3(64, 4), 0, st, op->geom, r, seg, X,
                        (const cplx_t<S>*)op->sc, op->code, B);
     gram_galerkin<S>(n, r, X, B, (const cplx_t<S>*)op->sc, part, out, st);
   };
@@ -442,7 +457,7 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
     // what Q = Q1 S2 spans (Q1^T Q1 = I up to about cond(P)^2 eps <= 1e-2 at
     // the drop threshold, so Q1^T A Q1 is as well conditioned as A_c); the
     // second pass is run only when the orthonormal basis is inspected.
-    gemm<double>((int)n, r, pu, P, ldp, S1, r, nullptr, ACT_NONE, (double*)c.Q.ptr, r, st);
+    basis(n, pu, r, P, ldp, S1, r == pu, (double*)c.Q.ptr, st);
     galerkin((const double*)c.Q.ptr, (double*)c.W1.ptr, Ac);
   } else {
     // fp32 stored basis (when requested, or for C64): CholeskyQR2, Q rounded
@@ -450,11 +465,11 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
     // G2 = Q1^T Q1, Cholesky without dropping -> S2 (r x r, into S1); its rank
     // record goes to info[2..3], read back with the inverse's record (every
     // kernel below is sized by r alone, so a lost rank only spoils values).
-    gemm<double>((int)n, r, pu, P, ldp, S1, r, nullptr, ACT_NONE, Q1, r, st);
+    basis(n, pu, r, P, ldp, S1, r == pu, Q1, st);
     gram(n, r, Q1, r, part, G2, st);
     chol_drop(r, G2, 0.0, 0, X, S1, info + 2, st);
     double* Q = (double*)c.W1.ptr;
-    gemm<double>((int)n, r, r, Q1, r, S1, r, nullptr, ACT_NONE, Q, r, st);
+    basis(n, r, r, Q1, r, S1, true, Q, st);
     // Q <- its stored values (rounded in place), then B in Q1
     hipLaunchKernelGGL((k_round_q<float>), dim3(ew_grid(n * r)), dim3(256), 0, st, n * (size_t)r, Q, (float*)c.Q.ptr);
     galerkin(Q, Q1, Ac);
@@ -514,7 +529,7 @@ helm_status coarse_orthonormal(helm_op_s* op, double* Qout, double* Acout, hipSt
   // second CholeskyQR pass: G2 = Q1^T Q1 = S2^-T S2^-1
   gram(n, r, Q1, r, part, G2, st);
   chol_drop(r, G2, 0.0, 0, X, S2, info + 2, st);
-  if (Qout) gemm<double>((int)n, r, r, Q1, r, S2, r, nullptr, ACT_NONE, Qout, r, st);
+  if (Qout) basis(n, r, r, Q1, r, S2, true, Qout, st);
   hipError_t e;
   if (Acout) {
     // A_c = Q^T A Q = S2^T (Q1^T A Q1) S2, formed in the work region, copied out

@@ -45,6 +45,9 @@ int small_ksplit(int K);
 template <typename T>
 void dense_small(int B, int N, int K, const T* x, const T* W, const T* bias, int act, T* y, double* part,
                  hipStream_t st);
+// Q = P S (P: n x K, row stride ldp; S: K x r, upper: upper triangular; r, K <= 128)
+void basis(size_t n, int K, int r, const double* P, size_t ldp, const double* S, bool upper, double* Q,
+           hipStream_t st);
 // out (r x r) = X^T X for X of n rows (row stride ldx), r <= 128; part: gram_part(n, r) doubles
 size_t gram_part(size_t n, int r);
 void gram(size_t n, int r, const double* X, size_t ldx, double* part, double* out, hipStream_t st);

@@ -1,4 +1,4 @@
-// Device pieces shared by the dense kernels (dense.hip, trunk.hip).
+// Device pieces shared by the dense kernels (dense.hip, trunk.hip, gram.hip).
 //
 // MFMA: v_mfma_f64_16x16x4f64.  Lane l supplies A[l % 16][l / 16] and
 // B[l / 16][l % 16] of a 16x4 by 4x16 product; its four accumulator registers
@@ -62,6 +62,77 @@ __device__ __forceinline__ T activate(T x, int act) {
   if (act == ACT_RELU) return x > T(0) ? x : T(0);
   if (act == ACT_LEAKY) return x > T(0) ? x : T(0.01) * x;
   return x;
+}
+
+constexpr int TRUNK_WAVES = 8;
+
+// One layer for RT x 16 rows and the CT column tiles wave, wave + 8 (16 columns
+// each): acc = H W over k < kend (a multiple of 8 DEPTH, at most W's K rows; columns
+// past N hold other columns' values or 0).  A from LDS, two consecutive k per 16-byte read: lane
+// group g = lane / 16 holds k = 8 c + 2 g + s of step s of chunk c, which is the
+// k its W rows are loaded from.  W comes straight from memory (1.8 MB at the
+// 3-256x4-128 trunk: it stays in every XCD's L2) into registers DEPTH chunks
+// ahead, so the k loop has no barrier.
+template <int RT, int CT>
+__device__ __forceinline__ void trunk_layer(const double* __restrict__ h, int lda, const double* __restrict__ W, int K,
+                                            int N, int wave, int lane, d4 (&acc)[RT][CT], int kend) {
+  constexpr int DEPTH = RT > 1 ? 2 : 4;
+  // buffer loads: a fixed lane offset and a uniform one that advances, so the
+  // loop carries one scalar for all of W's addresses
+  const __amdgpu_buffer_rsrc_t wr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(W), 0, 8 * K * N, 0x00020000);
+  const int wo = 8 * (2 * (lane >> 4) * N + (lane & 15));
+  int so = 128 * wave;
+  const double* ap = h + (lane & 15) * lda + 2 * (lane >> 4);
+  double bq[DEPTH][2][CT];
+  double2 av[2][RT];
+  // the scheduling barriers keep the loads here: W's DEPTH chunks ahead of
+  // their use, A's one
+  auto load = [&](int d) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int j = 0; j < CT; ++j)
+        bq[d][s][j] = __builtin_bit_cast(
+            double, __builtin_amdgcn_raw_buffer_load_b64(wr, wo + 128 * TRUNK_WAVES * j, so + 8 * s * N, 0));
+    so += 64 * N;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load_a = [&](int d) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) av[d][i] = *reinterpret_cast<const double2*>(ap + i * 16 * lda);
+    ap += 8;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](int d) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+          acc[i][j] = mfma16(s ? av[d & 1][i].y : av[d & 1][i].x, bq[d][s][j], acc[i][j]);
+  };
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int j = 0; j < CT; ++j) acc[i][j] = d4{0, 0, 0, 0};
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) load(d);
+  load_a(0);
+  for (int k = 8 * DEPTH; k < kend; k += 8 * DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      load_a((d + 1) & 1);
+      multiply(d);
+      load(d);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) {
+    if (d + 1 < DEPTH) load_a((d + 1) & 1);
+    multiply(d);
+  }
 }
 
 }  // namespace helm

@@ -1,4 +1,4 @@
-// Gram products of the coarse space's set-up: G = X^T X, and the Galerkin
+// Products of the coarse space's set-up: the basis Q = P S, G = X^T X, and the Galerkin
 // matrix X^T B - i X^T diag(Im s) X with B = (L - diag(Re s)) X, for X of n
 // rows and r <= 128 columns (App. C).  All three are symmetric (L is, and X
 // vanishes on masked rows), so only the 16 x 16 tiles on and above the diagonal are
@@ -192,6 +192,36 @@ __global__ __launch_bounds__(512) void k_gram_sum(int nb, int r, const double* _
   if (row >> 4 != col >> 4) put(col, row);
 }
 
+// Q = P S (P: n x K, row stride ldp; S: K x r; K a multiple of 16): 32 rows of P
+// through LDS, S from L2 into registers (trunk_layer), wavefront w the columns
+// 16 w .. + 15.  upper: S is upper triangular, so those columns need k < 16 (w + 1)
+// only.  Bound by the reading of P and the writing of Q (104 us at 64^3 x 128 at
+// 5.15 TB/s); the 128 x 128 tiles of k_gemm over all k, two barriers per 16 k, took
+// 216 us (106 at 56 x 48 x 52 x 96, 18 at 12960 x 48); this 157 (57, 6).
+__global__ __launch_bounds__(64 * TRUNK_WAVES, 6) void k_basis(size_t n, int K, int r, const double* __restrict__ P,
+                                                               size_t ldp, const double* __restrict__ S, int upper,
+                                                               double* __restrict__ Q) {
+  extern __shared__ __attribute__((aligned(16))) double h[];  // 32 x lda
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), lda = K + 2;
+  const size_t row0 = (size_t)blockIdx.x * 32;
+  for (int e = t; e < 32 * K; e += 64 * TRUNK_WAVES) {
+    const int i = e / K, k = e % K;
+    h[i * lda + k] = row0 + i < n ? P[(row0 + i) * ldp + k] : 0.0;
+  }
+  __syncthreads();
+  if (16 * wave >= r) return;
+  d4 acc[2][1];
+  trunk_layer<2, 1>(h, lda, S, K, r, wave, lane, acc, upper ? min(K, 16 * (wave + 1)) : K);
+  const int col = 16 * wave + (lane & 15);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const size_t row = row0 + 16 * a + acc_row(lane, i);
+      if (row < n && col < r) Q[row * r + col] = acc[a][0][i];
+    }
+}
+
 // One workgroup (eight wavefronts, two to a SIMD) per CU; fewer where a
 // workgroup would get less than 32 rows, one step or more for each share.
 static int gram_blocks(size_t n) { return (int)(n < 256 * 32 ? (n + 31) / 32 : 256); }
@@ -227,5 +257,17 @@ template void gram_galerkin<double>(size_t, int, const double*, const double*, c
                                     hipStream_t);
 template void gram_galerkin<float>(size_t, int, const double*, const double*, const cplx_t<float>*, double*, double*,
                                    hipStream_t);
+
+void basis(size_t n, int K, int r, const double* P, size_t ldp, const double* S, bool upper, double* Q,
+           hipStream_t st) {
+  if (K % 16) {  // k steps that S's rows do not fill
+    gemm<double>((int)n, r, K, P, ldp, S, r, nullptr, ACT_NONE, Q, r, st);
+    return;
+  }
+  kprof_begin(KP_MFMA, st);
+  hipLaunchKernelGGL(k_basis, dim3((unsigned)((n + 31) / 32)), dim3(64 * TRUNK_WAVES),
+                     32 * (K + 2) * sizeof(double), st, n, K, r, P, ldp, S, upper ? 1 : 0, Q);
+  kprof_end(KP_MFMA, (upper ? 1.0 : 2.0) * (double)n * K * r, st);
+}
 
 }  // namespace helm
