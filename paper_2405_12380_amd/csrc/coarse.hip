@@ -390,12 +390,11 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
   c.pass1 = !c.q_f32;  // fp64 basis: the first pass's basis is the one used
   if (!wide_t && (s = c.W1.ensure(n * (size_t)pu * sizeof(double)))) return s;
   if (c.q_f32 && (s = c.W2.ensure(n * (size_t)pu * sizeof(double)))) return s;
-  const size_t small_doubles = gram_part(n, pu) + 8 * (size_t)pu * pu + 4096;
+  const size_t small_doubles = gram_part(n, pu) + 7 * (size_t)pu * pu + 4096;
   if ((s = c.small.ensure(small_doubles * sizeof(double)))) return s;
   double* part = (double*)c.small.ptr;
   double* G = part + gram_part(n, pu);
-  double* X = G + (size_t)pu * pu;
-  double* S1 = X + (size_t)pu * pu;
+  double* S1 = G + (size_t)pu * pu;
   double* G2 = S1 + (size_t)pu * pu;
   double* gjw = G2 + (size_t)pu * pu;  // 4 pu^2
   int* info = (int*)(gjw + 4 * (size_t)pu * pu);
@@ -419,7 +418,7 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
   // pass 1: G = P^T P, Cholesky with dropping -> S1 (pu x r)
   gram(n, pu, P, ldp, part, G, st);
   const double tau = op->dt == HELM_C128 ? 1e-7 : 1e-5;
-  chol_drop(pu, G, tau * tau, 1, X, S1, info, st);
+  chol_drop(pu, G, tau * tau, 1, S1, info, st);
   hipError_t e = hipMemcpyAsync(op->host, info, 2 * sizeof(int), hipMemcpyDeviceToHost, st);
   if (e != hipSuccess) return hip_fail(e, "coarse: rank readback");
   if ((s = sync_stream(st, "coarse: pass 1"))) return s;
@@ -467,7 +466,7 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
     // kernel below is sized by r alone, so a lost rank only spoils values).
     basis(n, pu, r, P, ldp, S1, r == pu, Q1, st);
     gram(n, r, Q1, r, part, G2, st);
-    chol_drop(r, G2, 0.0, 0, X, S1, info + 2, st);
+    chol_drop(r, G2, 0.0, 0, S1, info + 2, st);
     double* Q = (double*)c.W1.ptr;
     basis(n, r, r, Q1, r, S1, true, Q, st);
     // Q <- its stored values (rounded in place), then B in Q1
@@ -520,15 +519,14 @@ helm_status coarse_orthonormal(helm_op_s* op, double* Qout, double* Acout, hipSt
   // the regions of the set-up's small buffer (laid out as in coarse_build)
   double* part = (double*)c.small.ptr;
   double* G = part + gram_part(n, pu);
-  double* X = G + (size_t)pu * pu;
-  double* S2 = X + (size_t)pu * pu;
+  double* S2 = G + (size_t)pu * pu;
   double* G2 = S2 + (size_t)pu * pu;
   double* gjw = G2 + (size_t)pu * pu;
   int* info = (int*)(gjw + 4 * (size_t)pu * pu);
   const double* Q1 = (const double*)c.Q.ptr;
   // second CholeskyQR pass: G2 = Q1^T Q1 = S2^-T S2^-1
   gram(n, r, Q1, r, part, G2, st);
-  chol_drop(r, G2, 0.0, 0, X, S2, info + 2, st);
+  chol_drop(r, G2, 0.0, 0, S2, info + 2, st);
   if (Qout) basis(n, r, r, Q1, r, S2, true, Qout, st);
   hipError_t e;
   if (Acout) {

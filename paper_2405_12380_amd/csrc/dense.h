@@ -57,9 +57,9 @@ template <typename S>
 void gram_galerkin(size_t n, int r, const double* X, const double* B, const cplx_t<S>* s, double* part, double* Ac,
                    hipStream_t st);
 // Cholesky with dropping of columns whose remaining squared norm is <= tau2 times
-// the largest squared column norm; G (p x p) is overwritten; X: p*p scratch;
-// S: p*p output capacity; info: 2 ints (rank, failed)
-void chol_drop(int p, double* G, double tau2, int allow_drop, double* X, double* S, int* info, hipStream_t st);
+// the largest squared column norm, G (p x p, symmetric, p <= 128) = P^T P; S:
+// p x rank so that P S is orthonormal (p * p capacity); info: 2 ints (rank, failed)
+void chol_drop(int p, const double* G, double tau2, int allow_drop, double* S, int* info, hipStream_t st);
 // inverse of the complex r x r matrix A (interleaved); work: 4*r*r doubles;
 // info: 1 int (1 = singular); cond: 1 double
 void gj_inverse(int r, const double* A, double* work, double* Ainv, int* info, double* cond, hipStream_t st);

@@ -177,160 +177,122 @@ __global__ void k_small_final(int B, int N, int ksplit, const double* __restrict
   y[e] = (T)activate<double>(acc, act);  // fp64 arithmetic, rounded once to the stored type
 }
 
+// one lane's value, wave-uniform; the largest of a wavefront
+__device__ __forceinline__ double lane_val(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_max(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return fmax(v, __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                                  __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false)));
+}
+__device__ __forceinline__ double wave_max(double v) {
+  v = dpp_max<0xB1>(dpp_max<0x4E>(dpp_max<0x141>(dpp_max<0x140>(v))));  // within the 16-lane rows
+  return fmax(fmax(lane_val(v, 0), lane_val(v, 16)), fmax(lane_val(v, 32), lane_val(v, 48)));
+}
+
 // ---- one-workgroup Cholesky with column dropping -------------------------------
-// G: p x p (row-major, fp64) = P^T P, p <= 128, factored in registers (16
-// entries per thread) and then kept in LDS for the triangular inverse (128 KiB
-// at p = 128; gfx950 gives a workgroup up to 160 KiB).  Right-looking Cholesky
-// G = R^T R on the upper triangle; a column whose Schur-complement diagonal is
-// <= tau2 * max_j G[j][j] is dropped (its remaining norm is at most tau times
-// the largest column norm), which matches Householder QR that skips such
-// columns.  R1^{-1} (kept rows/columns) is then formed in the free strictly
-// lower triangle (transposed) plus a diagonal array, one thread per column.
-// Outputs: S (p x r row-major) with S[kept[a]][:] = (R1^{-1})[a][:] and zero
+// G: p x p (symmetric, fp64) = P^T P, p <= 128.  G = R^T R column by column; a
+// column whose Schur-complement diagonal is <= tau2 * max_j G[j][j] is dropped (its
+// remaining norm is at most tau times the largest column norm), which matches
+// Householder QR that skips such columns.  Outputs: S (p x r row-major) with
+// S[kept[a]][:] = (R1^{-1})[a][:] (R1: the kept rows and columns of R) and zero
 // rows for dropped columns, so that Q = P S has orthonormal columns in exact
 // arithmetic; info[0] = r; info[1] = 1 if a column had to be dropped while
 // allow_drop = 0.
-__global__ __launch_bounds__(1024) void k_chol_drop(int p, const double* __restrict__ Gin, double tau2, int allow_drop,
+//
+// R1^{-1} comes out of the elimination itself: with G = L D L^T (L unit lower,
+// R = D^{1/2} L^T) the steps that turn G into D L^T turn I into L^{-1}, and
+// R1^{-1} = L^{-T} D^{-1/2}.  L^{-1} fills the lower triangle that the
+// elimination leaves free: step j takes (row a's entry j) / d_j times row j from
+// every row a > j (the still symmetric part of G right of column j, L^{-1} left of
+// it), and column j becomes minus that factor.  The matrix stays in registers:
+// thread (tx, ty) of a 32 x 32 grid holds rows tx + 32 v, columns ty + 32 u; row j is
+// published in LDS, double-buffered, one barrier per step.
+// What bounds it: the serial chain of p steps (row through LDS, reciprocal, the
+// next row's update).  Factoring with a square root and a division per step and
+// then inverting row by row in LDS took 241 us at p = 128 (75 at 48);
+// this takes 92 us (35).
+__global__ __launch_bounds__(1024) void k_chol_drop(int p, const double* __restrict__ G, double tau2, int allow_drop,
                                                     double* __restrict__ S, int* __restrict__ info) {
-  extern __shared__ double G[];  // p x p
-  __shared__ double xdiag[128];
-  __shared__ double rowj[2][128];  // row j of the factorization step, double-buffered
-  __shared__ int kept[128];
-  __shared__ int s_fail;
-  __shared__ double s_thr2;
-  const int t = threadIdx.x, nt = blockDim.x;
-  for (int e0 = 0; e0 < p * p; e0 += 4 * nt) {  // four loads in flight per thread
-    double v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = e0 + t + u * nt < p * p ? Gin[e0 + t + u * nt] : 0.0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (e0 + t + u * nt < p * p) G[e0 + t + u * nt] = v[u];
-  }
-  __syncthreads();
-  if (t == 0) {
-    s_fail = 0;
-    double mx = 0.0;  // largest squared column norm of P
-    for (int j = 0; j < p; ++j) mx = fmax(mx, G[j * p + j]);
-    s_thr2 = tau2 * mx;
-  }
-  __syncthreads();
-  const double thr2 = s_thr2;
-  // The matrix lives in registers during the factorization: thread (ty, tx) of
-  // a 32 x 32 grid holds G[ty + 32 u][tx + 32 v], u, v < 4.  Step j: the
-  // holders of row j (final after step j - 1) publish it unscaled in LDS
-  // (double-buffered, so one barrier per step), every thread takes the drop
-  // decision of column j itself from G[j][j] and updates its entries of the
-  // trailing upper triangle with R[j][a] R[j][c], R[j][c] = G[j][c] / piv
-  // formed as G[j][c] times the pivot's reciprocal; the holders of row j scale
-  // it in their registers.
-  const int ty = t >> 5, tx = t & 31;
+  __shared__ double rowj[2][128];
+  __shared__ double dpiv[128];  // d_j of a kept column
+  __shared__ int slot[128];     // its place among the kept columns; -1: dropped
+  __shared__ double s_max[2];
+  const int t = threadIdx.x, tx = t & 31, ty = t >> 5;
   double g[4][4];
 #pragma unroll
   for (int u = 0; u < 4; ++u)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int a = ty + 32 * u, c = tx + 32 * v;
-      g[u][v] = (a < p && c < p) ? G[a * p + c] : 0.0;
+      const int a = tx + 32 * v, c = ty + 32 * u;
+      g[u][v] = (a < p && c < p) ? G[c * p + a] : 0.0;
     }
+  if (t < 128) {  // largest squared column norm of P
+    const double m = wave_max(t < p ? G[t * p + t] : 0.0);
+    if ((t & 63) == 0) s_max[t >> 6] = m;
+  }
   int nk = 0;
+  bool fail = false;
+  double thr2 = 0.0;
   for (int j = 0; j < p; ++j) {
-    const int uj = j >> 5, buf = j & 1;
-    if (ty == (j & 31))
+    double* row = rowj[j & 1];
+    if (tx == (j & 31))
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (u == uj)
+      for (int v = 0; v < 4; ++v)
+        if (v == j >> 5)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int c = tx + 32 * v;
-            if (c < p) rowj[buf][c] = g[u][v];
-          }
+          for (int u = 0; u < 4; ++u) row[ty + 32 * u] = g[u][v];
     __syncthreads();
-    const double dj = rowj[buf][j];
+    if (j == 0) thr2 = tau2 * fmax(s_max[0], s_max[1]);
+    const double dj = row[j];
     const bool keep = dj > thr2;
-    const double piv = keep ? sqrt(dj) : -1.0;
     if (t == 0) {
-      if (keep) kept[nk] = j;
-      else if (!allow_drop) s_fail = 1;
+      slot[j] = keep ? nk : -1;
+      dpiv[j] = dj;
     }
     if (keep) {
       ++nk;
-      const double pinv = 1.0 / piv;
+      double ra[4], rc[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int a = ty + 32 * u;
-        if (a > j && a < p) {
-          const double ra = rowj[buf][a] * pinv;
+      for (int v = 0; v < 4; ++v) ra[v] = tx + 32 * v > j ? row[tx + 32 * v] : 0.0;
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int c = tx + 32 * v;
-            if (c >= a && c < p) g[u][v] -= ra * (rowj[buf][c] * pinv);
-          }
-        } else if (a == j) {
+      for (int u = 0; u < 4; ++u) rc[u] = row[ty + 32 * u];
+      const double dinv = 1.0 / dj;
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int c = tx + 32 * v;
-            if (c >= j && c < p) g[u][v] = (c == j) ? piv : g[u][v] * pinv;
-          }
-        }
+      for (int v = 0; v < 4; ++v) {
+        ra[v] *= dinv;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) g[u][v] = fma(-ra[v], rc[u], g[u][v]);
       }
-    }
-  }
+      if (ty == (j & 31))
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u)
+          if (u == j >> 5)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int a = ty + 32 * u, c = tx + 32 * v;
-      if (a < p && c < p) G[a * p + c] = g[u][v];
-    }
-  __syncthreads();
-  const int r = nk;
-  // X = R1^{-1}, R1[a][b] = G[kept[a]][kept[b]] (a <= b).  X[a][b] (a < b) is kept
-  // at G[kept[b]][kept[a]] (strictly lower, unused by R), X[a][a] in xdiag.
-  // Rows a = r-1 .. 0 in turn; column b of row a is formed by the 8 threads
-  // 8b .. 8b+7, which split the sum over c and combine it with three shuffles.
-  // Column b only reads its own earlier entries, written by the same 8 threads
-  // of one wavefront, so the steps are ordered within the wavefront alone.
-  {
-    const int b = t >> 3, sub = t & 7;
-    const bool colb = b < r && (t >> 3) < (nt >> 3);
-    const bool full = r == p;  // no column dropped: kept[c] = c, direct addressing
-    for (int a = r - 1; a >= 0; --a) {
-      double acc = 0.0;
-      if (colb && b >= a && full) {
-#pragma unroll 4
-        for (int c = a + 1 + sub; c < b; c += 8) acc += G[a * p + c] * G[b * p + c];
-        if (((b - a - 1) & 7) == sub && b > a) acc += G[a * p + b] * xdiag[b];
-      } else if (colb && b >= a)
-        for (int c = a + 1 + sub; c <= b; c += 8) {
-          const double xcb = (c == b) ? xdiag[b] : G[kept[b] * p + kept[c]];
-          acc += G[kept[a] * p + kept[c]] * xcb;
-        }
-      acc += __shfl_xor(acc, 4, 64);
-      acc += __shfl_xor(acc, 2, 64);
-      acc += __shfl_xor(acc, 1, 64);
-      if (colb && b >= a && sub == 0) {
-        const double v = ((a == b ? 1.0 : 0.0) - acc) / G[kept[a] * p + kept[a]];
-        if (a == b) xdiag[b] = v;
-        else G[kept[b] * p + kept[a]] = v;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-      __builtin_amdgcn_wave_barrier();
+            for (int v = 0; v < 4; ++v)
+              if (tx + 32 * v > j) g[u][v] = -ra[v];
+    } else {
+      fail |= !allow_drop;
     }
   }
   __syncthreads();
-  for (int e = t; e < p * r; e += nt) S[e] = 0.0;
-  __syncthreads();
-  for (int e = t; e < r * r; e += nt) {
-    const int a = e / r, b = e % r;
-    double v = 0.0;
-    if (a == b) v = xdiag[a];
-    else if (a < b) v = G[kept[b] * p + kept[a]];
-    S[(size_t)kept[a] * r + b] = v;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int a = tx + 32 * v, b = a < p ? slot[a] : -1;
+    if (b < 0) continue;
+    const double pinv = 1.0 / sqrt(dpiv[a]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = ty + 32 * u;
+      if (c < p) S[(size_t)c * nk + b] = c == a ? pinv : c < a && slot[c] >= 0 ? g[u][v] * pinv : 0.0;
+    }
   }
   if (t == 0) {
-    info[0] = r;
-    info[1] = s_fail;
+    info[0] = nk;
+    info[1] = fail;
   }
 }
 
@@ -356,21 +318,6 @@ __global__ __launch_bounds__(1024) void k_chol_drop(int p, const double* __restr
 // 563 instructions each, took 378 us at r = 128 (118 at 48); this one
 // takes 187 us (55 at 48).
 constexpr int GJ_P = 8;
-__device__ __forceinline__ double lane_val(double v, int lane) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                          __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_max(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  return fmax(v, __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
-                                  __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false)));
-}
-__device__ __forceinline__ double wave_max(double v) {
-  v = dpp_max<0xB1>(dpp_max<0x4E>(dpp_max<0x141>(dpp_max<0x140>(v))));  // within the 16-lane rows
-  return fmax(fmax(lane_val(v, 0), lane_val(v, 16)), fmax(lane_val(v, 32), lane_val(v, 48)));
-}
-
 // 1 / z, scaled by the exponent of the larger part (no overflow of |z|^2)
 __device__ __forceinline__ double2 crcp(double2 z) {
   const int k = -ilogb(fmax(fabs(z.x), fabs(z.y)));
@@ -652,16 +599,8 @@ void dense_small(int B, int N, int K, const T* x, const T* W, const T* bias, int
   hipLaunchKernelGGL((k_small_final<T>), dim3((B * N + 255) / 256), dim3(256), 0, st, B, N, ks, part, bias, act, y);
 }
 
-void chol_drop(int p, double* G, double tau2, int allow_drop, double* X, double* S, int* info, hipStream_t st) {
-  (void)X;
-  const size_t lds = sizeof(double) * (size_t)p * p;
-  static bool attr_set = false;
-  if (!attr_set) {
-    // G staged in LDS: up to 128 KiB at p = 128 (a gfx950 workgroup may use 160 KiB)
-    (void)hipFuncSetAttribute((const void*)k_chol_drop, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 128 * 8);
-    attr_set = true;
-  }
-  hipLaunchKernelGGL(k_chol_drop, dim3(1), dim3(1024), lds, st, p, G, tau2, allow_drop, S, info);
+void chol_drop(int p, const double* G, double tau2, int allow_drop, double* S, int* info, hipStream_t st) {
+  hipLaunchKernelGGL(k_chol_drop, dim3(1), dim3(1024), 0, st, p, G, tau2, allow_drop, S, info);
 }
 
 void gj_inverse(int r, const double* A, double* work, double* Ainv, int* info, double* cond, hipStream_t st) {
