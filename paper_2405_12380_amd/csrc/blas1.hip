@@ -721,6 +721,51 @@ __global__ void k_bicg_scalar(int step, BiState* bs, const double* red, BiState*
   }
 }
 
+// A reduction and the step it feeds in one launch: the sums of part's `width`
+// <= 3 columns, in k_reduce_cols's order, then bicg_step.  BI_RR's columns are ||r||^2
+// and the next rho, so BI_RHO follows it here, after the record is copied out (its
+// breakdown flag belongs to the next iteration).  At 56 x 48 x 52 a launch costs
+// about 3.3 us with its gap whatever it does; apart, the reductions and steps were
+// nine of an iteration's 31 launches; together they are four (gradient of 10
+// iterations each way there: 4268 -> 4135 us).
+__global__ __launch_bounds__(256) void k_bicg_reduce(int step, const double* __restrict__ part, int nparts, int width,
+                                                     BiState* bs, BiState* ghost) {
+  __shared__ double sh[16];
+  double red[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    if (w >= width) continue;
+    double acc = 0.0;
+    for (int b0 = 0; b0 < nparts; b0 += 4 * 256) {
+      double v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int b = b0 + threadIdx.x + 256 * q;
+        v[q] = b < nparts ? part[(size_t)b * width + w] : 0.0;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc += v[q];
+    }
+    red[w] = acc;
+  }
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    if (w >= width) continue;
+    red[w] = block_sum(red[w], sh);
+  }
+  if (threadIdx.x != 0) return;
+  bicg_step(step, bs, red);
+  if (ghost) {
+    *ghost = *bs;
+    __threadfence_system();
+  }
+  if (step == BI_RR) bicg_step(BI_RHO, bs, red + 1);
+}
+
+void bicg_reduce(int step, const double* part, int nparts, int width, BiState* bs, hipStream_t st, BiState* ghost) {
+  hipLaunchKernelGGL(k_bicg_reduce, dim3(1), dim3(256), 0, st, step, part, nparts, width, bs, ghost);
+}
+
 void bicg_scalar(int step, BiState* bs, const double* red, hipStream_t st, BiState* ghost) {
   hipLaunchKernelGGL(k_bicg_scalar, dim3(1), dim3(64), 0, st, step, bs, red, ghost);
 }

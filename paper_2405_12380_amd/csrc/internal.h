@@ -121,7 +121,11 @@ void bicg_update(size_t n, const void* ph, const void* sh, const void* s, const 
                  void* r, const BiState* bs, double* part, hipStream_t st);  // part: 3 per block: rr, rhat^H r
 template <typename S>
 void axpy_dev(size_t n, const void* x, void* y, const double* a, hipStream_t st);  // y += a x, a complex on device
-// scalar steps (single thread), reading the reduced values in `red`
+// scalar steps, on part's column sums (nparts x width <= 3; BI_RR takes ||r||^2 and
+// the next rho and does BI_RHO too, after the copy to ghost) or on the reduced
+// values in `red` (BI_INIT)
+void bicg_reduce(int step, const double* part, int nparts, int width, BiState* bs, hipStream_t st,
+                 BiState* ghost = nullptr);
 void bicg_scalar(int step, BiState* bs, const double* red, hipStream_t st, BiState* ghost = nullptr);
 // BI_INIT starts a sweep: rho0 = alpha = omega = 1, the rest 0, flag 0, and
 // red[0], red[1] (||f||^2 and ||r||^2 of the sweep's start) left in fn and rr

@@ -421,8 +421,8 @@ helm_status bicgstab_drive(helm_op_s* op, MetaCtx& c, const void* f, void* u, me
     if (status != HELM_NOT_CONVERGED) break;
     // rho for the first iteration of this sweep
     dot_part<S>(n, rh, r, part, st);
-    reduce_cols(part, rdb, 2, red + 8, st);
-    // One iteration = half 1 (rho, p, M p, v = A M p, alpha, s, ||s||) and
+    bicg_reduce(BI_RHO, part, rdb, 2, bs, st);
+    // One iteration (its rho known) = half 1 (p, M p, v = A M p, alpha, s, ||s||) and
     // half 2 (M s, t = A M s, omega, the updates of u and r, ||r||).  Each half
     // ends by writing the state record to pinned memory behind an event.  Half 1
     // of the next iteration is queued before the host looks at ||r||: if ||r||
@@ -433,7 +433,6 @@ helm_status bicgstab_drive(helm_op_s* op, MetaCtx& c, const void* f, void* u, me
     BiState* dS = (BiState*)(op->host_dev + 256);  // the same records, as the kernels address them
     BiState* dR = (BiState*)(op->host_dev + 320);
     auto half1 = [&](bool first_) -> helm_status {
-      bicg_scalar(BI_RHO, bs, red + 8, st);
       bicg_p<S>(n, r, v, p, bs, first_ ? 1 : 0, st);
       if (c.use_M) {
         helm_status e2 = precond_apply<S>(op, c, p, ph, st);
@@ -441,11 +440,9 @@ helm_status bicgstab_drive(helm_op_s* op, MetaCtx& c, const void* f, void* u, me
       }
       stencil_apply<S>(op->geom, op->sc, op->code, ph, v, st);
       dot_part<S>(n, rh, v, part, st);
-      reduce_cols(part, rdb, 2, red, st);
-      bicg_scalar(BI_ALPHA, bs, red, st);
+      bicg_reduce(BI_ALPHA, part, rdb, 2, bs, st);
       bicg_s<S>(n, r, v, sv, bs, part, st);
-      reduce_cols(part, rdb, 1, red + 2, st);
-      bicg_scalar(BI_SS, bs, red + 2, st, dS);
+      bicg_reduce(BI_SS, part, rdb, 1, bs, st, dS);
       hipError_t e1 = hipEventRecord(ev[0], st);
       return e1 == hipSuccess ? launch_check("bicgstab: half 1") : hip_fail(e1, "bicgstab: half 1 record");
     };
@@ -493,11 +490,9 @@ helm_status bicgstab_drive(helm_op_s* op, MetaCtx& c, const void* f, void* u, me
       stencil_apply<S>(op->geom, op->sc, op->code, sh, t, st);
       matvecs++;
       two_dot_part<S>(n, t, sv, part, st);
-      reduce_cols(part, rdb, 3, red + 4, st);
-      bicg_scalar(BI_OMEGA, bs, red + 4, st);
+      bicg_reduce(BI_OMEGA, part, rdb, 3, bs, st);
       bicg_update<S>(n, ph, sh, sv, t, rh, u, r, bs, part, st);
-      reduce_cols(part, rdb, 3, red + 8 - 1, st);  // red[7] = ||r||^2, red[8..9] = r_hat^H r (next rho)
-      bicg_scalar(BI_RR, bs, red + 7, st, dR);
+      bicg_reduce(BI_RR, part, rdb, 3, bs, st, dR);  // ||r||^2 and r_hat^H r (next rho)
       e1 = hipEventRecord(ev[1], st);
       if (e1 != hipSuccess) return hip_fail(e1, "bicgstab: half 2 record");
       // look ahead: the next half 1, unless ||s|| scaled by the last second
