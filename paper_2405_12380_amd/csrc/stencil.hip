@@ -16,6 +16,8 @@
 // ((c - x_minus) + (c - x_plus)) / h_a^2 are accumulated x, y, z in turn and
 // s_p c is subtracted last, in fp64 for both storage precisions.
 #include "common.h"
+
+#include <type_traits>
 #include "internal.h"
 #include "prof.h"
 #include "stencil_dev.h"
@@ -203,8 +205,8 @@ constexpr int RB_RROW = (RB_TX + 2) / 2, RB_NRED = RB_RROW * (RB_TY + 2);  // re
 // rim), one black update on the first 256 (the tile's 256 black nodes), the
 // staged plane three positions per thread
 constexpr int RB_NT = 384, RB_NB = RB_TX * RB_TY / 2;
-constexpr int RB_QP = (RB_PL + RB_NT - 1) / RB_NT, RB_RU = (RB_NRED + RB_NT - 1) / RB_NT;
-static_assert(RB_NB <= RB_NT && RB_RU == 1, "ring tile sizes");
+constexpr int RB_QP = (RB_PL + RB_NT - 1) / RB_NT;
+static_assert(RB_NB <= RB_NT && RB_NRED <= RB_NT, "ring tile sizes");
 
 // A node's data for one relaxation update: the aligned 32-bit word that holds
 // its code byte (a word, not the byte, so that a value carried into the next
@@ -214,8 +216,6 @@ struct NodeIn {
   unsigned cw;
   double2 s, f;
 };
-__device__ __forceinline__ unsigned rb_cw_off(unsigned boff) { return boff & ~3u; }
-__device__ __forceinline__ unsigned rb_cd(unsigned cw, unsigned boff) { return (cw >> (8 * (boff & 3u))) & 0xffu; }
 
 template <typename S, int DEPTH>
 __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, const cplx_t<S>* __restrict__ sc,
@@ -230,26 +230,51 @@ __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, cons
   const int gx0 = bx * RB_TX - 2, gy0 = by * RB_TY - 2;  // global (x, y) of LDS position (0, 0)
   const int z0 = bz * zb, z1 = min(g.nz, z0 + zb);
   const int t = threadIdx.x;
-  const size_t nxy = (size_t)g.nx * g.ny, nn = nxy * g.nz;
-  const __amdgpu_buffer_rsrc_t r_u = rb_rsrc(uin, nn * sizeof(C)), r_f = rb_rsrc(f, nn * sizeof(C)),
-                               r_s = rb_rsrc(sc, nn * sizeof(C)), r_c = rb_rsrc(code, (nn + 3) & ~(size_t)3),
-                               r_o = rb_rsrc(uout, nn * sizeof(C));
-  auto slot = [](int k) { return (k + RB_NS) % RB_NS; };  // k >= -RB_NS
-  // node index of LDS position e in plane k, or -1 where there is no node
-  auto node = [&](int e, int k) -> long {
-    const int gx = gx0 + e % RB_LX, gy = gy0 + e / RB_LX;
-    return (k >= 0 && k < g.nz && gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny)
-               ? (long)((size_t)gx + (size_t)g.nx * gy + nxy * k)
-               : -1L;
+  const unsigned nxy = (unsigned)g.nx * g.ny, nn = nxy * g.nz;
+  constexpr unsigned ESZ = sizeof(C), ABSENT = RB_OOB / ESZ;  // ABSENT >= nn, as ESZ nn < 2^31
+  // the fields, empty (loads give 0, stores are dropped) for a plane that is
+  // not there or not to be stored; a plane's offset is the scalar part of the
+  // address, 0 with an empty field (it must stay below the buffer's size)
+  auto rsrc = [](const void* p, unsigned bytes, bool there) {
+    return rb_rsrc(p, __builtin_amdgcn_readfirstlane(there ? bytes : 0));
   };
-  auto boff = [](long p, unsigned esz) { return p >= 0 ? (unsigned)p * esz : RB_OOB; };
+  auto there = [&](int k) { return k >= 0 && k < g.nz; };
+  auto first = [&](int k) { return there(k) ? (unsigned)k * nxy : 0u; };  // plane k's first node
+  auto slot = [](int k) { return (k + RB_NS) % RB_NS; };  // k >= -RB_NS
+  // LDS position e's node within its plane
+  auto node = [&](int e) -> unsigned {
+    const int gx = gx0 + e % RB_LX, gy = gy0 + e / RB_LX;
+    return gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny ? (unsigned)(gx + g.nx * gy) : ABSENT;
+  };
+  // Everything about a thread's nodes but their plane is formed once: the
+  // staged positions' offsets, and for planes of either parity its red and its
+  // black node's LDS position, node within the plane and store offset.  Formed
+  // anew each step, the addresses were a third of a step's instructions (157 x
+  // 142 x 131 in fp32: 75 -> 63 us a sweep).
+  unsigned pv[RB_QP];
+#pragma unroll
+  for (int q = 0; q < RB_QP; ++q) pv[q] = t + RB_NT * q < RB_PL ? node(t + RB_NT * q) * ESZ : RB_OOB;
+  const bool bact = t < RB_NB;  // a black node of the tile (32 per row, 8 rows)
+  int re[2], be[2];
+  unsigned rv[2], bv[2], ro[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int r = t < RB_NRED ? t : RB_NRED - 1;
+    const int ly = 1 + r / RB_RROW, lx = 1 + ((gx0 + 1 + gy0 + ly + k) & 1) + 2 * (r % RB_RROW);
+    re[k] = ly * RB_LX + lx;
+    rv[k] = t < RB_NRED ? node(re[k]) : ABSENT;
+    const bool tile = lx >= 2 && lx < RB_TX + 2 && ly >= 2 && ly < RB_TY + 2;
+    ro[k] = tile ? rv[k] * ESZ : RB_OOB;  // the rim's values are the neighbouring tile's to store
+    const int tb = bact ? t : t - RB_NB;
+    const int my = 2 + tb / (RB_TX / 2), mx = 3 - ((gx0 + gy0 + my + k) & 1) + 2 * (tb % (RB_TX / 2));
+    be[k] = my * RB_LX + mx;
+    bv[k] = bact ? node(be[k]) : ABSENT;
+  }
   // staged plane k: thread t holds LDS positions t + RB_NT q (zero where there is no node)
   auto load_plane = [&](int k, double2 (&pre)[RB_QP]) {
+    const __amdgpu_buffer_rsrc_t r_u = rsrc(uin, nn * ESZ, there(k));
 #pragma unroll
-    for (int q = 0; q < RB_QP; ++q) {
-      const int e = t + RB_NT * q;
-      pre[q] = rb_ld(r_u, boff(e < RB_PL ? node(e, k) : -1L, sizeof(C)), (const C*)nullptr);
-    }
+    for (int q = 0; q < RB_QP; ++q) pre[q] = rb_ld(r_u, pv[q], first(k) * ESZ, (const C*)nullptr);
   };
   auto store_plane = [&](int k, const double2 (&pre)[RB_QP]) {
     double2* P = ring[slot(k)];
@@ -257,57 +282,28 @@ __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, cons
     for (int q = 0; q < RB_QP; ++q)
       if (t + RB_NT * q < RB_PL) P[t + RB_NT * q] = pre[q];
   };
-  // red node r (< RB_NRED) of plane k: LDS position on the tile or its one-node rim
-  auto red_pos = [&](int r, int k) {
-    const int ly = 1 + r / RB_RROW, c = r % RB_RROW;
-    const int lx = 1 + ((gx0 + 1 + gy0 + ly + k) & 1) + 2 * c;
-    return ly * RB_LX + lx;
+  auto load_node = [&](unsigned v, int k, NodeIn& in) {
+    in.cw = __builtin_amdgcn_raw_buffer_load_b32(rsrc(code, (nn + 3) & ~3u, there(k)), (v + first(k)) & ~3u, 0, 0);
+    in.s = rb_ld(rsrc(sc, nn * ESZ, there(k)), v * ESZ, first(k) * ESZ, (const C*)nullptr);
+    in.f = rb_ld(rsrc(f, nn * ESZ, there(k)), v * ESZ, first(k) * ESZ, (const C*)nullptr);
   };
-  // black node of plane k owned by thread t < RB_NB (32 per row, 8 rows); the
-  // other threads address a valid position and store nothing
-  const bool bact = t < RB_NB;
-  const int tb = bact ? t : t - RB_NB;
-  auto black_pos = [&](int k) {
-    const int ly = 2 + tb / (RB_TX / 2), c = tb % (RB_TX / 2);
-    const int lx = 3 - ((gx0 + gy0 + ly + k) & 1) + 2 * c;
-    return ly * RB_LX + lx;
+  // the code byte of node v of plane k in its word
+  auto code_of = [&](unsigned cw, unsigned v, int k) { return __builtin_amdgcn_ubfe(cw, 8 * ((v + first(k)) & 3), 8); };
+  // node data of a step's red update (plane kr) and black update (plane kb), of parities pr and pb
+  auto load_next = [&](int kr, int pr, int kb, int pb, NodeIn& rn, NodeIn& bn) {
+    load_node(rv[pr], kr, rn);
+    load_node(bv[pb], kb, bn);
   };
-  auto load_node = [&](long p, NodeIn& in) {
-    in.cw = __builtin_amdgcn_raw_buffer_load_b32(r_c, rb_cw_off(boff(p, 1)), 0, 0);
-    in.s = rb_ld(r_s, boff(p, sizeof(C)), (const C*)nullptr);
-    in.f = rb_ld(r_f, boff(p, sizeof(C)), (const C*)nullptr);
-  };
-  // this thread's u-th red node of plane k: LDS position, node index (-1: none)
-  auto red_node = [&](int u, int k, int& e) -> long {
-    const int r = t + RB_NT * u;
-    e = red_pos(r < RB_NRED ? r : RB_NRED - 1, k);
-    return r < RB_NRED ? node(e, k) : -1L;
-  };
-  // node data of a step's red updates (plane kr) and black update (plane kb)
-  auto load_next = [&](int kr, int kb, NodeIn (&rn)[RB_RU], NodeIn& bn) {
-#pragma unroll
-    for (int u = 0; u < RB_RU; ++u) {
-      int e;
-      load_node(red_node(u, kr, e), rn[u]);
-    }
-    load_node(bact ? node(black_pos(kb), kb) : -1L, bn);
-  };
-  // red half-sweep of plane k; the tile's values go to uout when `own`
-  auto red = [&](int k, const NodeIn* in, bool own) {
+  // red half-sweep of plane k (parity pk); the tile's values go to uout when `own`
+  auto red = [&](int k, int pk, const NodeIn& in, bool own) {
     double2* P = ring[slot(k)];
-    const double2* Pm = ring[slot(k - 1)];
-    const double2* Pp = ring[slot(k + 1)];
-#pragma unroll
-    for (int u = 0; u < RB_RU; ++u) {
-      int e;
-      const long p = red_node(u, k, e);
-      const double2 v = rnd_store<S>(relax_upd<S>(g, rb_cd(in[u].cw, boff(p, 1)), P[e], P[e - 1], P[e + 1], P[e - RB_LX], P[e + RB_LX],
-                                                  Pm[e], Pp[e], in[u].s, in[u].f, omega, true));
-      if (p >= 0) P[e] = v;
-      const int lx = e % RB_LX, ly = e / RB_LX;
-      const bool tile = lx >= 2 && lx < RB_TX + 2 && ly >= 2 && ly < RB_TY + 2;
-      rb_st(r_o, boff(own && tile ? p : -1L, sizeof(C)), v, (C*)nullptr);
-    }
+    const int e = re[pk];
+    const double2 v = rnd_store<S>(relax_upd<S>(g, code_of(in.cw, rv[pk], k), P[e], P[e - 1], P[e + 1], P[e - RB_LX],
+                                                P[e + RB_LX], ring[slot(k - 1)][e], ring[slot(k + 1)][e], in.s, in.f,
+                                                omega, true));
+    if (there(k) && rv[pk] != ABSENT) P[e] = v;
+    own = own && there(k);
+    rb_st_cached(rsrc(uout, nn * ESZ, own), ro[pk], own ? first(k) * ESZ : 0u, v, (C*)nullptr);
   };
   // prologue: planes z0 - 2 .. z0 + 2 staged, plane z0 + 3 in flight, red of z0 - 1 and z0
   // Prefetch depth DEPTH: step z reads the register set loaded DEPTH - 1 steps
@@ -318,50 +314,54 @@ __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, cons
   // loads).  The kernel runs with DEPTH = 2; depths 3 and 4 measured no faster.
   struct Pre {
     double2 pl[RB_QP];
-    NodeIn rn[RB_RU], bn;
+    NodeIn rn, bn;
   };
   Pre S_[DEPTH];
-  NodeIn r0[RB_RU], r1[RB_RU];
-  for (int k = z0 - 2; k <= z0 + 2; ++k) {
-    load_plane(k, S_[0].pl);
-    store_plane(k, S_[0].pl);
-  }
+  NodeIn r0, r1;
+  // march(P): z0 has parity P, so that a step's parities are constants (the
+  // loop is unrolled by an even DEPTH)
+  static_assert(DEPTH % 2 == 0, "a step's parity follows its place in the unrolled loop");
+  auto march = [&](auto par) {
+    constexpr int P0 = decltype(par)::value;
+    for (int k = z0 - 2; k <= z0 + 2; ++k) {
+      load_plane(k, S_[0].pl);
+      store_plane(k, S_[0].pl);
+    }
+    load_node(rv[1 - P0], z0 - 1, r0);
+    load_node(rv[P0], z0, r1);
 #pragma unroll
-  for (int u = 0; u < RB_RU; ++u) {
-    int e;
-    load_node(red_node(u, z0 - 1, e), r0[u]);
-    load_node(red_node(u, z0, e), r1[u]);
-  }
-#pragma unroll
-  for (int j = 0; j < DEPTH - 1; ++j) {
-    load_plane(z0 + 3 + j, S_[j].pl);
-    load_next(z0 + 1 + j, z0 + j, S_[j].rn, S_[j].bn);
-  }
-  __syncthreads();
-  red(z0 - 1, r0, false);
-  red(z0, r1, true);
-  auto step = [&](int z, const Pre& cur, Pre& nxt) {
-    store_plane(z + 3, cur.pl);  // its slot last held plane z - 3
-    load_plane(z + DEPTH + 2, nxt.pl);
-    load_next(z + DEPTH, z + DEPTH - 1, nxt.rn, nxt.bn);
-    red(z + 1, cur.rn, z + 1 < z1);
+    for (int j = 0; j < DEPTH - 1; ++j) {
+      load_plane(z0 + 3 + j, S_[j].pl);
+      load_next(z0 + 1 + j, (P0 + 1 + j) & 1, z0 + j, (P0 + j) & 1, S_[j].rn, S_[j].bn);
+    }
     __syncthreads();
-    // black half-sweep of plane z on the tile (wavefronts of the first 256 threads)
-    if (bact) {
-      const int e = black_pos(z);
-      const double2* P = ring[slot(z)];
-      const double2 v = relax_upd<S>(g, rb_cd(cur.bn.cw, boff(node(e, z), 1)), P[e], P[e - 1], P[e + 1],
-                                     P[e - RB_LX], P[e + RB_LX], ring[slot(z - 1)][e], ring[slot(z + 1)][e],
-                                     cur.bn.s, cur.bn.f, omega, true);
-      rb_st(r_o, boff(z < z1 ? node(e, z) : -1L, sizeof(C)), v, (C*)nullptr);
+    red(z0 - 1, 1 - P0, r0, false);
+    red(z0, P0, r1, true);
+    auto step = [&](int z, int pz, const Pre& cur, Pre& nxt) {
+      store_plane(z + 3, cur.pl);  // its slot last held plane z - 3
+      load_plane(z + DEPTH + 2, nxt.pl);
+      load_next(z + DEPTH, pz, z + DEPTH - 1, 1 - pz, nxt.rn, nxt.bn);
+      red(z + 1, 1 - pz, cur.rn, z + 1 < z1);
+      __syncthreads();
+      // black half-sweep of plane z on the tile (wavefronts of the first 256 threads)
+      if (bact) {
+        const int e = be[pz];
+        const double2* P = ring[slot(z)];
+        const double2 v = relax_upd<S>(g, code_of(cur.bn.cw, bv[pz], z), P[e], P[e - 1], P[e + 1], P[e - RB_LX],
+                                       P[e + RB_LX], ring[slot(z - 1)][e], ring[slot(z + 1)][e], cur.bn.s, cur.bn.f,
+                                       omega, true);
+        rb_st_cached(rsrc(uout, nn * ESZ, z < z1), bv[pz] * ESZ, z < z1 ? first(z) * ESZ : 0u, v, (C*)nullptr);
+      }
+    };
+    // the march is rounded up to a multiple of DEPTH steps: the steps past z1
+    // store nothing (no branches around them, so the register sets stay put)
+    for (int z = z0; z < z1; z += DEPTH) {
+#pragma unroll
+      for (int i = 0; i < DEPTH; ++i) step(z + i, (P0 + i) & 1, S_[i], S_[(i + DEPTH - 1) % DEPTH]);
     }
   };
-  // the march is rounded up to a multiple of DEPTH steps: the steps past z1
-  // store nothing (no branches around them, so the register sets stay put)
-  for (int z = z0; z < z1; z += DEPTH) {
-#pragma unroll
-    for (int i = 0; i < DEPTH; ++i) step(z + i, S_[i], S_[(i + DEPTH - 1) % DEPTH]);
-  }
+  if (z0 & 1) march(std::integral_constant<int, 1>{});
+  else march(std::integral_constant<int, 0>{});
 }
 
 template <typename S>
@@ -505,12 +505,26 @@ void stencil_rbgs_fused(const StencilGeom& g0, const void* sc, const uint8_t* co
   const bool small = n * esz < 2147483648.0;
   const bool ring = g.dim == 3 && (g.rb == 1 || (g.rb == 0 && small));
   if (ring) {
-    // planes per workgroup: about 1024 workgroups, marches of 2 .. 64 planes
-    // (at 256^3 the 32-plane marches measured best, 304 against 314-362 us for
-    // 48-96 planes; at 384^3 64 planes, 989 against 1035 us for 32)
+    // planes per workgroup.  Large grids: about 1024 workgroups, marches of 32 .. 64
+    // planes (at 256^3 the 32-plane marches measured best, 304 against 314-362 us
+    // for 48-96 planes; at 384^3 64 planes, 989 against 1035 us for 32).  Grids that
+    // would march less than 32 planes: the length with the fewest steps, counting
+    // a march's prologue as three and rounds of the 512 workgroups that run at
+    // once (two per CU, by their LDS); at 157 x 142 x 131 in fp32 15 planes in one
+    // round take 57 us a sweep, 6 planes in three rounds 63.
     const long tiles = (long)((g.nx + RB_TX - 1) / RB_TX) * ((g.ny + RB_TY - 1) / RB_TY);
     int zb = (int)(tiles * g.nz / 1024);
-    zb = zb < 2 ? 2 : zb > 64 ? 64 : zb;
+    if (zb > 64) zb = 64;
+    if (zb < 32) {
+      long least = -1;
+      for (int c = 2; c <= 64; ++c) {
+        const long cost = (tiles * ((g.nz + c - 1) / c) + 511) / 512 * (c + 3);
+        if (least < 0 || cost < least) {
+          least = cost;
+          zb = c;
+        }
+      }
+    }
     const long nbr = tiles * ((g.nz + zb - 1) / zb);
     hipLaunchKernelGGL((k_rbgs_ring<S, 2>), dim3((unsigned)nbr), dim3(RB_NT), 0, st, g, zb, (const C*)sc, code,
                        (const C*)uin, (const C*)f, (C*)uout, omega);

@@ -353,11 +353,11 @@ __device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off,
   const float2 v = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, so, 0));
   return make_double2((double)v.x, (double)v.y);
 }
-__device__ __forceinline__ void rb_st(__amdgpu_buffer_rsrc_t r, unsigned off, double2 v, double2*) {
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(rb_u4, v), r, off, 0, 0);
+__device__ __forceinline__ void rb_st_cached(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned so, double2 v, double2*) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(rb_u4, v), r, off, so, 0);
 }
-__device__ __forceinline__ void rb_st(__amdgpu_buffer_rsrc_t r, unsigned off, double2 v, float2*) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(rb_u2, make_float2((float)v.x, (float)v.y)), r, off, 0, 0);
+__device__ __forceinline__ void rb_st_cached(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned so, double2 v, float2*) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(rb_u2, make_float2((float)v.x, (float)v.y)), r, off, so, 0);
 }
 
 // streaming (non-temporal) stores

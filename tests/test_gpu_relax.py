@@ -58,3 +58,25 @@ def test_masked_and_nonfinite_values_stay_apart():
         g = to_np(u)
         assert np.isfinite(g[~m.ravel()]).all()
         assert not np.isfinite(g[m.ravel()]).any()
+
+
+@pytest.mark.parametrize("dtype", [helm.C128, helm.C64])
+@pytest.mark.parametrize("n", [
+    (64, 8, 4), (65, 9, 3), (3, 5, 3),        # marches of an even and an odd number of planes; a tile, a node more
+    (131, 70, 67), (190, 66, 130),            # marches that start on planes of either parity
+    (157, 142, 131),                          # one round of 15-plane marches
+])
+def test_rbgs_marches_equal_pairs(n, dtype):
+    """The red-black ring kernel, whatever the length and first plane of its
+    marches, gives the register-pair kernel's values bit for bit."""
+    P = I.random_problem(n, sum(n), mask_frac=0.08, k=6.0)
+    lo = dtype == helm.C64
+    op = make_op(helm, P, dtype)
+    f = op.field(P["f"])
+    out = []
+    for which in (helm.RB_PAIRS, helm.RB_RING):
+        op.set_rbgs_kernel(which)
+        u = op.field(stored(P["x"], lo))
+        op.relax(helm.RBGS, 0.9, 3, f, u)
+        out.append(to_np(u))
+    assert np.array_equal(out[0], out[1])
