@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -30,7 +31,7 @@ namespace helm {
 namespace {
 
 constexpr int EB_CH = 2048;     // elements per element-wise workgroup (256 threads x 8)
-constexpr size_t QB_ROWS = 2048;  // basis rows per skinny-product workgroup
+constexpr size_t QB_MAX = 128;     // a problem's skinny-product workgroups at most
 constexpr int SEG_ALIGN = 256;  // element alignment of each problem's segment
 constexpr int ITERS_PER_GRAPH = 4;
 
@@ -373,15 +374,41 @@ __global__ __launch_bounds__(256) void kb_state(int step, const BProb* __restric
 }
 
 // ---- trunk-basis correction ----------------------------------------------------
+// The batch's bases are larger than the caches together: streaming loads, 16
+// bytes a lane where a problem's rows are 16-byte aligned.  f(lanes per row, load
+// form) as constants.
+template <typename T, typename F>
+__device__ __forceinline__ void by_row_form(int r, F f) {
+  auto lanes = [&](auto ld) {
+    switch (qt_lanes(r, sizeof(T))) {
+      case 8: f(std::integral_constant<int, 8>{}, ld); break;
+      case 16: f(std::integral_constant<int, 16>{}, ld); break;
+      case 32: f(std::integral_constant<int, 32>{}, ld); break;
+      default: f(std::integral_constant<int, 64>{}, ld);
+    }
+  };
+  if (r * sizeof(T) % 16) lanes(std::integral_constant<int, LD_VALUES>{});
+  else lanes(std::integral_constant<int, LD_STREAM>{});
+}
+
+// Restriction and prolongation, a problem's workgroups sweeping its basis
+// together.  Bound by reading the bases: eight of 48^3 .. 80^3 x 128 (2.3 GB) took
+// 439 and 472 us with lanes owning columns l and l + 64 of 8 bytes and one group of
+// rows in flight; they take 360 (6.3 TB/s) and 396 us.
 template <typename T, typename S>
-__global__ __launch_bounds__(256) void kb_qt(const BProb* __restrict__ P, const BState* __restrict__ B,
-                                             const int* __restrict__ qmap, const cplx_t<S>* __restrict__ x,
-                                             double* __restrict__ part) {
+__global__ __launch_bounds__(64 * QT_WAVES) void kb_qt(const BProb* __restrict__ P, const BState* __restrict__ B,
+                                                       const int* __restrict__ qmap, const cplx_t<S>* __restrict__ x,
+                                                       double* __restrict__ part) {
+  __shared__ double sh[QT_WAVES][256];
   const int p = qmap[blockIdx.x];
   if (!running(B[p])) return;
   const BProb& q = P[p];
-  const size_t i0 = (size_t)(blockIdx.x - q.qb0) * QB_ROWS;
-  qt_rows<T, S>(q.rank, (const T*)q.Q, x + q.off, i0, min(q.n, i0 + QB_ROWS), part + (size_t)blockIdx.x * 256);
+  const size_t wave = (size_t)QT_WAVES * (blockIdx.x - q.qb0) + (threadIdx.x >> 6);
+  by_row_form<T>(q.rank, [&](auto lpr, auto ld) {
+    qt_sweep<T, S, decltype(lpr)::value, decltype(ld)::value>(q.n, q.rank, (const T*)q.Q, x + q.off, wave,
+                                                              (size_t)QT_WAVES * q.qbn, sh,
+                                                              part + (size_t)blockIdx.x * 256);
+  });
 }
 
 // y_p = sum of the problem's Q^T partials (fixed order), then c_p = A_c^{-1} y_p
@@ -425,15 +452,17 @@ __global__ __launch_bounds__(64) void kb_ainv(const BProb* __restrict__ P, const
 }
 
 template <typename T, typename S>
-__global__ __launch_bounds__(256) void kb_skinny(const BProb* __restrict__ P, const BState* __restrict__ B,
-                                                 const int* __restrict__ qmap, const double* __restrict__ c,
-                                                 cplx_t<S>* __restrict__ z) {
+__global__ __launch_bounds__(64 * QT_WAVES) void kb_skinny(const BProb* __restrict__ P, const BState* __restrict__ B,
+                                                           const int* __restrict__ qmap, const double* __restrict__ c,
+                                                           cplx_t<S>* __restrict__ z) {
   const int p = qmap[blockIdx.x];
   if (!running(B[p])) return;
   const BProb& q = P[p];
-  const size_t wave = 4 * (size_t)(blockIdx.x - q.qb0) + (threadIdx.x >> 6);
-  skinny_rows<T, S, SK_ADD>(q.n, q.rank, (const T*)q.Q, c + (size_t)p * 256, z + q.off, q.mask, nullptr, wave,
-                            4 * (size_t)q.qbn);
+  const size_t wave = (size_t)QT_WAVES * (blockIdx.x - q.qb0) + (threadIdx.x >> 6);
+  by_row_form<T>(q.rank, [&](auto lpr, auto ld) {
+    skinny_sweep<T, S, SK_ADD, decltype(lpr)::value, decltype(ld)::value>(
+        q.n, q.rank, (const T*)q.Q, c + (size_t)p * 256, z + q.off, q.mask, nullptr, wave, (size_t)QT_WAVES * q.qbn);
+  });
 }
 
 // ---- host side -------------------------------------------------------------------
@@ -461,7 +490,7 @@ static void pack(std::vector<BProb>& pr, const std::vector<int>& list, Packing& 
     q.ebn = (int)((q.n + EB_CH - 1) / EB_CH);
     pk.emap.insert(pk.emap.end(), q.ebn, i);
     q.qb0 = (int)pk.qmap.size();
-    q.qbn = q.rank > 0 ? (int)((q.n + QB_ROWS - 1) / QB_ROWS) : 0;
+    q.qbn = q.rank > 0 ? (int)std::min((q.n + 64 * QT_WAVES - 1) / (64 * QT_WAVES), QB_MAX) : 0;
     pk.qmap.insert(pk.qmap.end(), q.qbn, i);
   }
 }
@@ -515,10 +544,10 @@ struct BatchRun {
     }
     if (nqb > 0) {
       stencil_launch(ST_RESID, z, vin, r1, st);
-      hipLaunchKernelGGL((kb_qt<T, S>), dim3(nqb), dim3(256), 0, st, dP, dB, dqmap, r1, pq);
+      hipLaunchKernelGGL((kb_qt<T, S>), dim3(nqb), dim3(64 * QT_WAVES), 0, st, dP, dB, dqmap, r1, pq);
       hipLaunchKernelGGL(kb_qreduce, dim3(np), dim3(256), 0, st, dP, dB, pq, ybuf);
       hipLaunchKernelGGL(kb_ainv, dim3(np * 128), dim3(64), 0, st, dP, dB, ybuf, cbuf);
-      hipLaunchKernelGGL((kb_skinny<T, S>), dim3(nqb), dim3(256), 0, st, dP, dB, dqmap, cbuf, z);
+      hipLaunchKernelGGL((kb_skinny<T, S>), dim3(nqb), dim3(64 * QT_WAVES), 0, st, dP, dB, dqmap, cbuf, z);
     }
   }
 

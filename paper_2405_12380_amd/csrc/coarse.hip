@@ -31,11 +31,6 @@
 namespace helm {
 
 static constexpr size_t QT_MAXB = 256;
-// lanes that read one row of r columns of esz-byte values, 16 bytes each
-static int qt_lanes(int r, size_t esz) {
-  const int need = (int)((r * esz + 15) / 16);
-  return need <= 8 ? 8 : need <= 16 ? 16 : need <= 32 ? 32 : 64;
-}
 // How a basis is loaded: through the caches up to 192 MB, where most of it is
 // still in the 256 MB memory-side cache at the next pass (56 x 48 x 52, r = 96,
 // 107 MB: one inversion step 4870 us, against 5170 streaming); streaming
@@ -59,8 +54,9 @@ template <typename T, typename S, int LPR, int LD>
 __global__ __launch_bounds__(64 * QT_WAVES) void k_qt_part(size_t n, int r, const T* __restrict__ Q,
                                                            const cplx_t<S>* __restrict__ x,
                                                            double* __restrict__ part) {
+  __shared__ double sh[QT_WAVES][256];
   qt_sweep<T, S, LPR, LD>(n, r, Q, x, (blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6,
-                      ((size_t)gridDim.x * blockDim.x) >> 6, part + (size_t)blockIdx.x * 2 * r);
+                          ((size_t)gridDim.x * blockDim.x) >> 6, sh, part + (size_t)blockIdx.x * 2 * r);
 }
 
 // y = the sum of the restriction's nb partials (in a fixed order), c = Ainv y
