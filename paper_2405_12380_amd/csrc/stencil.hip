@@ -232,14 +232,18 @@ __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, cons
   const int t = threadIdx.x;
   const unsigned nxy = (unsigned)g.nx * g.ny, nn = nxy * g.nz;
   constexpr unsigned ESZ = sizeof(C), ABSENT = RB_OOB / ESZ;  // ABSENT >= nn, as ESZ nn < 2^31
-  // the fields, empty (loads give 0, stores are dropped) for a plane that is
-  // not there or not to be stored; a plane's offset is the scalar part of the
-  // address, 0 with an empty field (it must stay below the buffer's size)
-  auto rsrc = [](const void* p, unsigned bytes, bool there) {
-    return rb_rsrc(p, __builtin_amdgcn_readfirstlane(there ? bytes : 0));
+  // A plane: its first node and a mask of the fields' sizes.  For one that is not
+  // there or not to be stored both are 0: the fields are empty (loads give 0,
+  // stores are dropped), and the scalar part of the address stays below the
+  // buffer's size.  The mask goes through readfirstlane, so that a step has no
+  // branches on it (they made it wait for its own prefetches).
+  struct Plane {
+    unsigned ok, n0;
   };
-  auto there = [&](int k) { return k >= 0 && k < g.nz; };
-  auto first = [&](int k) { return there(k) ? (unsigned)k * nxy : 0u; };  // plane k's first node
+  auto plane = [&](int k, bool on = true) -> Plane {
+    const unsigned ok = __builtin_amdgcn_readfirstlane(on && k >= 0 && k < g.nz ? ~0u : 0u);
+    return {ok, ok & ((unsigned)k * nxy)};
+  };
   auto slot = [](int k) { return (k + RB_NS) % RB_NS; };  // k >= -RB_NS
   // LDS position e's node within its plane
   auto node = [&](int e) -> unsigned {
@@ -250,7 +254,7 @@ __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, cons
   // staged positions' offsets, and for planes of either parity its red and its
   // black node's LDS position, node within the plane and store offset.  Formed
   // anew each step, the addresses were a third of a step's instructions (157 x
-  // 142 x 131 in fp32: 75 -> 63 us a sweep).
+  // 142 x 131 in fp32: 70 -> 63 us a sweep).
   unsigned pv[RB_QP];
 #pragma unroll
   for (int q = 0; q < RB_QP; ++q) pv[q] = t + RB_NT * q < RB_PL ? node(t + RB_NT * q) * ESZ : RB_OOB;
@@ -272,9 +276,10 @@ __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, cons
   }
   // staged plane k: thread t holds LDS positions t + RB_NT q (zero where there is no node)
   auto load_plane = [&](int k, double2 (&pre)[RB_QP]) {
-    const __amdgpu_buffer_rsrc_t r_u = rsrc(uin, nn * ESZ, there(k));
+    const Plane l = plane(k);
+    const __amdgpu_buffer_rsrc_t r_u = rb_rsrc(uin, nn * ESZ & l.ok);
 #pragma unroll
-    for (int q = 0; q < RB_QP; ++q) pre[q] = rb_ld(r_u, pv[q], first(k) * ESZ, (const C*)nullptr);
+    for (int q = 0; q < RB_QP; ++q) pre[q] = rb_ld(r_u, pv[q], l.n0 * ESZ, (const C*)nullptr);
   };
   auto store_plane = [&](int k, const double2 (&pre)[RB_QP]) {
     double2* P = ring[slot(k)];
@@ -283,12 +288,13 @@ __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, cons
       if (t + RB_NT * q < RB_PL) P[t + RB_NT * q] = pre[q];
   };
   auto load_node = [&](unsigned v, int k, NodeIn& in) {
-    in.cw = __builtin_amdgcn_raw_buffer_load_b32(rsrc(code, (nn + 3) & ~3u, there(k)), (v + first(k)) & ~3u, 0, 0);
-    in.s = rb_ld(rsrc(sc, nn * ESZ, there(k)), v * ESZ, first(k) * ESZ, (const C*)nullptr);
-    in.f = rb_ld(rsrc(f, nn * ESZ, there(k)), v * ESZ, first(k) * ESZ, (const C*)nullptr);
+    const Plane l = plane(k);
+    in.cw = __builtin_amdgcn_raw_buffer_load_b32(rb_rsrc(code, (nn + 3) & ~3u & l.ok), (v + l.n0) & ~3u, 0, 0);
+    in.s = rb_ld(rb_rsrc(sc, nn * ESZ & l.ok), v * ESZ, l.n0 * ESZ, (const C*)nullptr);
+    in.f = rb_ld(rb_rsrc(f, nn * ESZ & l.ok), v * ESZ, l.n0 * ESZ, (const C*)nullptr);
   };
   // the code byte of node v of plane k in its word
-  auto code_of = [&](unsigned cw, unsigned v, int k) { return __builtin_amdgcn_ubfe(cw, 8 * ((v + first(k)) & 3), 8); };
+  auto code_of = [&](unsigned cw, unsigned v, int k) { return __builtin_amdgcn_ubfe(cw, 8 * ((v + plane(k).n0) & 3), 8); };
   // node data of a step's red update (plane kr) and black update (plane kb), of parities pr and pb
   auto load_next = [&](int kr, int pr, int kb, int pb, NodeIn& rn, NodeIn& bn) {
     load_node(rv[pr], kr, rn);
@@ -301,9 +307,9 @@ __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, cons
     const double2 v = rnd_store<S>(relax_upd<S>(g, code_of(in.cw, rv[pk], k), P[e], P[e - 1], P[e + 1], P[e - RB_LX],
                                                 P[e + RB_LX], ring[slot(k - 1)][e], ring[slot(k + 1)][e], in.s, in.f,
                                                 omega, true));
-    if (there(k) && rv[pk] != ABSENT) P[e] = v;
-    own = own && there(k);
-    rb_st_cached(rsrc(uout, nn * ESZ, own), ro[pk], own ? first(k) * ESZ : 0u, v, (C*)nullptr);
+    if (rv[pk] != ABSENT) P[e] = v;  // a plane that is not there holds no neighbour of a node's
+    const Plane l = plane(k, own);
+    rb_st_cached(rb_rsrc(uout, nn * ESZ & l.ok), ro[pk], l.n0 * ESZ, v, (C*)nullptr);
   };
   // prologue: planes z0 - 2 .. z0 + 2 staged, plane z0 + 3 in flight, red of z0 - 1 and z0
   // Prefetch depth DEPTH: step z reads the register set loaded DEPTH - 1 steps
@@ -350,7 +356,8 @@ __global__ __launch_bounds__(RB_NT) void k_rbgs_ring(StencilGeom g, int zb, cons
         const double2 v = relax_upd<S>(g, code_of(cur.bn.cw, bv[pz], z), P[e], P[e - 1], P[e + 1], P[e - RB_LX],
                                        P[e + RB_LX], ring[slot(z - 1)][e], ring[slot(z + 1)][e], cur.bn.s, cur.bn.f,
                                        omega, true);
-        rb_st_cached(rsrc(uout, nn * ESZ, z < z1), bv[pz] * ESZ, z < z1 ? first(z) * ESZ : 0u, v, (C*)nullptr);
+        const Plane l = plane(z, z < z1);
+        rb_st_cached(rb_rsrc(uout, nn * ESZ & l.ok), bv[pz] * ESZ, l.n0 * ESZ, v, (C*)nullptr);
       }
     };
     // the march is rounded up to a multiple of DEPTH steps: the steps past z1
@@ -505,26 +512,21 @@ void stencil_rbgs_fused(const StencilGeom& g0, const void* sc, const uint8_t* co
   const bool small = n * esz < 2147483648.0;
   const bool ring = g.dim == 3 && (g.rb == 1 || (g.rb == 0 && small));
   if (ring) {
-    // planes per workgroup.  Large grids: about 1024 workgroups, marches of 32 .. 64
-    // planes (at 256^3 the 32-plane marches measured best, 304 against 314-362 us
-    // for 48-96 planes; at 384^3 64 planes, 989 against 1035 us for 32).  Grids that
-    // would march less than 32 planes: the length with the fewest steps, counting
-    // a march's prologue as three and rounds of the 512 workgroups that run at
-    // once (two per CU, by their LDS); at 157 x 142 x 131 in fp32 15 planes in one
-    // round take 57 us a sweep, 6 planes in three rounds 63.
+    // planes per workgroup: the march length (2 .. 64) with the fewest steps,
+    // counting a march's prologue as three and rounds of the 512 workgroups that run
+    // at once (two per CU, by their LDS); a length from 32 on within 5% of it if there
+    // is one (the shortest).  Measured in us a sweep: 157 x 142 x 131 in fp32 15
+    // planes (one round) 46, 6 planes (three rounds) 57; fp64 200 x 180 x 160 32
+    // planes 111, 15 planes 125; 256^3 32 planes 276, 64 planes 303, 40-55 307-317;
+    // 320^3 32 planes 597, 62 planes (five marches of 62 and one of 10) 628; 384^3 55
+    // planes 962, 64 planes 980, 32 planes 1018.
     const long tiles = (long)((g.nx + RB_TX - 1) / RB_TX) * ((g.ny + RB_TY - 1) / RB_TY);
-    int zb = (int)(tiles * g.nz / 1024);
-    if (zb > 64) zb = 64;
-    if (zb < 32) {
-      long least = -1;
-      for (int c = 2; c <= 64; ++c) {
-        const long cost = (tiles * ((g.nz + c - 1) / c) + 511) / 512 * (c + 3);
-        if (least < 0 || cost < least) {
-          least = cost;
-          zb = c;
-        }
-      }
-    }
+    auto steps = [&](int c) { return (tiles * ((g.nz + c - 1) / c) + 511) / 512 * (c + 3); };
+    int zb = 2;
+    for (int c = 3; c <= 64; ++c)
+      if (steps(c) < steps(zb)) zb = c;
+    for (int c = 32; c < zb; ++c)
+      if (20 * steps(c) <= 21 * steps(zb)) zb = c;
     const long nbr = tiles * ((g.nz + zb - 1) / zb);
     hipLaunchKernelGGL((k_rbgs_ring<S, 2>), dim3((unsigned)nbr), dim3(RB_NT), 0, st, g, zb, (const C*)sc, code,
                        (const C*)uin, (const C*)f, (C*)uout, omega);
