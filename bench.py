@@ -36,7 +36,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # kernel class -> source file that defines its kernel (for the traffic record's validity)
 KERNEL_SOURCE = {"qt_part": ("coarse.hip", "coarse_dev.h"), "skinny_apply": ("coarse.hip", "coarse_dev.h"),
                  "cgs_fused": ("blas1.hip",), "multidot": ("blas1.hip",), "multi_axpy": ("blas1.hip",),
-                 "stencil": ("stencil.hip", "stencil_dev.h"), "mfma_setup": ("dense.hip", "dense.h")}
+                 "stencil": ("stencil.hip", "relax.hip", "stencil_dev.h"), "mfma_setup": ("trunk.hip", "gram.hip", "dense.hip", "dense_dev.h")}
 
 
 def measured_traffic(kernel, grid_n):
@@ -243,7 +243,8 @@ def main():
                for k, v in kp.items()}
     if dom == "mfma_setup":
         achieved = (tot / max(cnt, 1)) / (per_launch_ms * 1e-3) / 1e12
-        roofline = {"bound": "mfma", "kernel": "k_gemm + k_gram (fp64 MFMA set-up products)",
+        roofline = {"bound": "mfma", "kernel": "set-up products: k_basis + k_gram (fp64 MFMA), trunk (fixed point on int8 "
+                                              "MFMA, counted as the fp64 flop it stands for)",
                     "achieved": round(achieved, 2), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(achieved / FP64_PEAK_TFLOPS, 4), "traffic": measured_traffic(dom, n[0]),
                     "flops_per_launch": tot / max(cnt, 1), "avg_launch_us": round(per_launch_ms * 1e3, 2),
@@ -664,8 +665,8 @@ def adjoint_gradient(helm, I, torch, dev, N, fd_dirs):
 def stencil_bandwidth(helm, I, torch, dev, N, reps=40):
     """Per-launch duration of each stencil kernel at N^3 (complex128), from the
     library's event timing, against algorithmic bytes (49 B/node for apply,
-    65 B/node for residual, a Jacobi sweep and a red-black sweep, which runs as
-    one fused pass)."""
+    65 B/node for residual, a Jacobi sweep, two Jacobi sweeps in one pass and a
+    red-black sweep, which runs as one fused pass)."""
     n = (N, N, N)
     nn = N ** 3
     g = np.random.default_rng(1)
@@ -675,9 +676,10 @@ def stencil_bandwidth(helm, I, torch, dev, N, reps=40):
     f = torch.randn(nn, dtype=torch.complex128, device=dev)
     y = torch.empty_like(x)
     runs = {"apply": lambda: op.apply(x, y), "residual": lambda: op.residual(f, x, y),
-            "jacobi": lambda: op.relax(helm.JACOBI, 0.5, 2, f, x),
+            "jacobi": lambda: op.relax(helm.JACOBI, 0.5, 1, f, x),
+            "jacobi_pair": lambda: op.relax(helm.JACOBI, 0.5, 2, f, x),
             "rbgs": lambda: op.relax(helm.RBGS, 1.0, 2, f, x)}
-    by = {"apply": 49.0, "residual": 65.0, "jacobi": 65.0, "rbgs": 65.0}
+    by = {"apply": 49.0, "residual": 65.0, "jacobi": 65.0, "jacobi_pair": 65.0, "rbgs": 65.0}
     out = {"grid": N}
     for name, fn in runs.items():
         fn()
@@ -688,7 +690,7 @@ def stencil_bandwidth(helm, I, torch, dev, N, reps=40):
         torch.cuda.synchronize()
         cnt, ms, tot = helm.kprof_read(helm.KP_STENCIL)
         helm.kprof_enable(False)
-        us = 1e3 * ms / cnt   # one launch per sweep (red-black: one fused pass)
+        us = 1e3 * ms / cnt   # one launch per run and sweep, or per pair of Jacobi sweeps
         gbs = by[name] * nn / (us * 1e-6) / 1e9
         out[name] = {"us": round(us, 1), "GBps": round(gbs, 1), "frac_peak": round(gbs / HBM_PEAK_GBS, 3)}
     # copy ceiling: the library's non-temporal streaming copy of 2 GiB (read +
