@@ -346,7 +346,7 @@ static helm_status trunk_eval(don_s* net, helm_op_s* op, T* out, hipStream_t st)
     const std::vector<void*>& Wf = wide ? net->tW : net->tW64;
     const std::vector<void*>& Bf = wide ? net->tB : net->tB64;
     trunk_fused<T>(op->dim, op->n, L, net->tw.data(), (const double* const*)Wf.data(), (const double* const*)Bf.data(),
-                   map_act(net->act), net->fix_ok ? net->tfix : nullptr, out, st);
+                   map_act(net->act), out, st);
     return launch_check("trunk");
   }
   int maxw = 1;
@@ -383,26 +383,6 @@ static helm_status trunk_eval(don_s* net, helm_op_s* op, T* out, hipStream_t st)
     }
   }
   return launch_check("trunk");
-}
-
-helm_status don_trunk_digits(don_s* net, hipStream_t st) {
-  const int L = (int)net->tw.size() - 1;
-  net->fix_ok = false;
-  // other activations are unbounded (an infinity has no digits)
-  if (map_act(net->act) != ACT_TANH || !trunk_fused_fits(L, net->tw.data())) return HELM_OK;
-  helm_status s = HELM_OK;
-  if (!net->tfix && (s = dalloc(&net->tfix, trunk_fix_bytes(L, net->tw.data())))) return s;
-  const std::vector<void*>& W = net->dt == HELM_C128 ? net->tW : net->tW64;
-  const std::vector<void*>& B = net->dt == HELM_C128 ? net->tB : net->tB64;
-  const int* flag = trunk_fix_build(L, net->tw.data(), (const double* const*)W.data(), (const double* const*)B.data(),
-                                    net->tfix, st);
-  if ((s = launch_check("trunk digits"))) return s;
-  int bad = 1;
-  hipError_t e = hipMemcpyAsync(&bad, flag, sizeof(int), hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e != hipSuccess) return hip_fail(e, "trunk digits");
-  net->fix_ok = bad == 0;
-  return HELM_OK;
 }
 
 helm_status don_trunk(don_s* net, helm_op_s* op, void* out, hipStream_t st) {
@@ -645,7 +625,6 @@ helm_status deeponet_load(helm_dtype dt, const don_desc* d, const double* const*
       net->tB64.push_back(b64);
     }
   }
-  if (!s) s = don_trunk_digits(net, nullptr);
   if (s) {
     deeponet_free(net);
     return s;
@@ -662,7 +641,6 @@ void deeponet_free(don_net net) {
   for (void* p : net->tB) dfree(p);
   for (void* p : net->tW64) dfree(p);
   for (void* p : net->tB64) dfree(p);
-  dfree(net->tfix);
   net->act0.release();
   net->act1.release();
   net->tact0.release();

@@ -20,19 +20,12 @@ void coord_layer(int dim, const int n[3], size_t row0, size_t nrows, const T* W,
 // out = the trunk matrix T (nn x w[L], row-major) of the grid's nodes: all L layers
 // (W[l]: w[l] x w[l + 1], hidden activation act, last layer linear) in one
 // launch, fp64 arithmetic, rounded once to T as stored.  Only for widths that
-// trunk_fused_fits accepts.  fix: the weights' digits (trunk_fix_build), or NULL
-// for products in fp64.
+// trunk_fused_fits accepts.
 constexpr int TRUNK_MAXL = 8;
 bool trunk_fused_fits(int L, const int* w);
-// fixed-point digits of the weights of a tanh trunk, built in buf
-// (trunk_fix_bytes); the int returned (on the device) is nonzero if these weights
-// need the fp64 products instead
-size_t trunk_fix_bytes(int L, const int* w);
-const int* trunk_fix_build(int L, const int* w, const double* const* W, const double* const* b, void* buf,
-                           hipStream_t st);
 template <typename T>
 void trunk_fused(int dim, const int n[3], int L, const int* w, const double* const* W, const double* const* b, int act,
-                 const void* fix, T* out, hipStream_t st);
+                 T* out, hipStream_t st);
 // C = act(A W + bias) (fp64 MFMA; instantiated for double); bias may be NULL;
 // act = ACT_NONE for linear
 template <typename T>

@@ -26,11 +26,10 @@ __device__ __forceinline__ int acc_row(int lane, int i) { return (lane >> 4) + 4
 // reciprocal of t + 1 in [1, 2^63] and one correction.  27 fp64 instructions, where
 // the library expm1 and a general division take about 60: fp64 work adds to the
 // time of the matrix products beside it.  Past |x| = 22 the result is 1; NaN
-// stays NaN unless the caller rules it out (NANS).
-template <bool NANS = true>
+// stays NaN.
 __device__ __forceinline__ double tanh_fast(double x) {
   const double ax = fabs(x);
-  const double y = NANS ? (ax > 22.0 ? 22.0 : ax) : fmin(ax, 22.0);
+  const double y = ax > 22.0 ? 22.0 : ax;
   const double m = fma(y, 2.8853900817779268, 6755399441055744.0), n = m - 6755399441055744.0;
   double r = fma(n, -0.34657359027997264, y);
   r = fma(n, -1.1600963245594897e-17, r);

@@ -93,8 +93,6 @@ struct don_s {
   std::vector<int> bw, tw;
   std::vector<void*> bW, bB, tW, tB;
   std::vector<void*> tW64, tB64;
-  void* tfix = nullptr;     // digits of the trunk's weights for its fixed-point products
-  bool fix_ok = false;      // they serve these weights
   int serial = 0;
   helm::Buffer act0, act1;  // branch activations (small) and trunk chunks
   helm::Buffer tact0, tact1;
@@ -110,8 +108,6 @@ helm_status op_part(helm_op_s* op, size_t doubles, double** out);
 // Validate that `net` can act on `op` (grid dimension, dtype) with p_used columns.
 helm_status check_net_for_op(const don_s* net, const helm_op_s* op, int p_used);
 int don_p(const don_s* net);
-// The trunk's weights were written: rebuild their digits (enqueued on st, which it waits for).
-helm_status don_trunk_digits(don_s* net, hipStream_t st);
 int don_serial(const don_s* net);
 // A fresh serial number (weights changed: cached trunk matrices and coarse spaces go stale).
 void don_touch(don_s* net);

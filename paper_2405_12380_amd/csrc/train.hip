@@ -1663,9 +1663,7 @@ helm_status don_train_export(don_trainer t, don_net net, void* stream) {
                          m + y.offW, (double*)net->tW64[i]);
       hipLaunchKernelGGL(k_cvt_back<double>, dim3(1), dim3(256), 0, t->st, 1, y.N, m + y.offb, (double*)net->tB64[i]);
     }
-  helm_status s = launch_check("don_train_export");
-  if (!s) s = don_trunk_digits(net, t->st);
-  if (!s) s = sync(t, "don_train_export");
+  helm_status s = sync(t, "don_train_export");
   if (s) return s;
   don_touch(net);
   return launch_check("don_train_export");
