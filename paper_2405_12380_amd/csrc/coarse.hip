@@ -121,14 +121,14 @@ __global__ __launch_bounds__(256) void k_skinny(size_t n, int r, const T* __rest
 // fetched for each of its three planes), node ranges by XCD 206, this 173 (89 -> 57
 // at 56 x 48 x 52 x 96, 376 -> 281 at 80 x 72 x 76 x 128).
 template <typename S, int V>
-__global__ __launch_bounds__(256) void k_batched_lap(StencilGeom g, int r, int seg, const double* __restrict__ Q,
+__global__ __launch_bounds__(256) void k_batched_lap(StencilGeom g, int r, int seg, size_t w0, const double* __restrict__ Q,
                                                      const cplx_t<S>* __restrict__ sc, const uint8_t* __restrict__ code,
                                                      double* __restrict__ B) {
   typedef double dv __attribute__((ext_vector_type(V)));
   const size_t nxy = (size_t)g.nx * g.ny, ry = (size_t)g.nx * r, rz = nxy * r;
-  // logical wavefront: segment fastest
+  // logical wavefront, from w0 on: segment fastest
   const unsigned nseg = (g.nz + seg - 1) / seg;
-  const size_t lw = (size_t)xcd_remap(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.y);
+  const size_t lw = w0 + (size_t)xcd_remap(blockIdx.x, gridDim.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.y);
   const size_t q = lw / nseg;
   if (q >= nxy) return;
   const int z0 = (int)(lw % nseg) * seg, z1 = min(g.nz, z0 + seg);
@@ -441,8 +441,11 @@ static helm_status coarse_build(helm_op_s* op, don_s* net, int p_used, bool qf32
     const size_t nxy = n / op->geom.nz, want = (8192 + nxy - 1) / nxy;
     const int seg = std::max(1, (int)(op->geom.nz / want));
     const size_t waves = nxy * ((op->geom.nz + seg - 1) / seg);
-    hipLaunchKernelGGL(lap, dim3((unsigned)((waves + 3) / 4)), dim3(64, 4), 0, st, op->geom, r, seg, X,
-                       (const cplx_t<S>*)op->sc, op->code, B);
+    // 2^26 wavefronts per launch (a 2D grid has one per node): below 2^32 work-items on an axis
+    constexpr size_t WMAX = (size_t)1 << 26;
+    for (size_t w0 = 0; w0 < waves; w0 += WMAX)
+      hipLaunchKernelGGL(lap, dim3((unsigned)((std::min(waves - w0, WMAX) + 3) / 4)), dim3(64, 4), 0, st, op->geom, r,
+                         seg, w0, X, (const cplx_t<S>*)op->sc, op->code, B);
     gram_galerkin<S>(n, r, X, B, (const cplx_t<S>*)op->sc, part, out, st);
   };
   double* Ac = (double*)c.Ac.ptr;

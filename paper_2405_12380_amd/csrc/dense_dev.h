@@ -64,6 +64,11 @@ __device__ __forceinline__ T activate(T x, int act) {
 }
 
 constexpr int TRUNK_WAVES = 8;
+// Workgroups of TRUNK_WAVES wavefronts as 32 x 16 threads: a launch has fewer
+// than 2^32 work-items on an axis, and a grid of 2^31 nodes in 32-row blocks
+// has 2^26 workgroups.
+inline dim3 trunk_block() { return dim3(32, 2 * TRUNK_WAVES); }
+__device__ __forceinline__ int trunk_thread() { return threadIdx.x + 32 * threadIdx.y; }
 
 // One layer for RT x 16 rows and the CT column tiles wave, wave + 8 (16 columns
 // each): acc = H W over k < kend (a multiple of 8 DEPTH, at most W's K rows; columns

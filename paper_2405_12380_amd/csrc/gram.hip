@@ -202,7 +202,7 @@ __global__ __launch_bounds__(64 * TRUNK_WAVES, 6) void k_basis(size_t n, int K, 
                                                                size_t ldp, const double* __restrict__ S, int upper,
                                                                double* __restrict__ Q) {
   extern __shared__ __attribute__((aligned(16))) double h[];  // 32 x lda
-  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), lda = K + 2;
+  const int t = trunk_thread(), lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), lda = K + 2;
   const size_t row0 = (size_t)blockIdx.x * 32;
   for (int e = t; e < 32 * K; e += 64 * TRUNK_WAVES) {
     const int i = e / K, k = e % K;
@@ -265,7 +265,7 @@ void basis(size_t n, int K, int r, const double* P, size_t ldp, const double* S,
     return;
   }
   kprof_begin(KP_MFMA, st);
-  hipLaunchKernelGGL(k_basis, dim3((unsigned)((n + 31) / 32)), dim3(64 * TRUNK_WAVES),
+  hipLaunchKernelGGL(k_basis, dim3((unsigned)((n + 31) / 32)), trunk_block(),
                      32 * (K + 2) * sizeof(double), st, n, K, r, P, ldp, S, upper ? 1 : 0, Q);
   kprof_end(KP_MFMA, (upper ? 1.0 : 2.0) * (double)n * K * r, st);
 }

@@ -79,7 +79,7 @@ __global__ __launch_bounds__(64 * TRUNK_WAVES, RT > 2 ? 2 : 4) void k_trunk(Trun
   constexpr int ROWS = 16 * RT;
   extern __shared__ __attribute__((aligned(16))) double h[];  // ROWS x lda activations
   __shared__ double xc[ROWS][3];
-  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int t = trunk_thread(), lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const size_t row0 = (size_t)blockIdx.x * ROWS;
   if (t < ROWS) {
     const size_t p = row0 + t < a.nn ? row0 + t : a.nn - 1;  // rows past the end repeat the last node
@@ -121,7 +121,7 @@ static void trunk_launch(const TrunkArgs& a, T* out, hipStream_t st) {
   const size_t rows = 16 * RT, lds = rows * a.lda * sizeof(double);
   // per launch, not once per process: the limit is kept per device
   (void)hipFuncSetAttribute((const void*)k_trunk<RT, T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL((k_trunk<RT, T>), dim3((unsigned)((a.nn + rows - 1) / rows)), dim3(64 * TRUNK_WAVES), lds, st, a,
+  hipLaunchKernelGGL((k_trunk<RT, T>), dim3((unsigned)((a.nn + rows - 1) / rows)), trunk_block(), lds, st, a,
                      out);
 }
 
