@@ -16,15 +16,17 @@
 
 namespace helm {
 
-// ---- 2D: up to JT_MAX sweeps, the tile in LDS -------------------------------------
+// ---- 2D: several sweeps, the tile in LDS -------------------------------------------
 // A workgroup holds a 32 x 32 region (512 threads, two nodes each: f, s, the
 // code and the reciprocal diagonal stay in registers over the sweeps, u
 // ping-pongs through LDS) and stores the part that t sweeps leave valid:
 // 32 - 2 t nodes on an axis, all of them on an axis of at most 32 nodes, where
 // the region needs no rim.  Eight sweeps leave a 16 x 16 tile of the 32 x 32:
 // four times the arithmetic, in a sixth of the launches (25 sweeps: 96 -> 27 us
-// at 64 x 64, 50 us at 400 x 400).
-constexpr int JT = 32, JT_MAX = 8, JT_NT = 512, JT_N = JT * JT / JT_NT, JT_LD = JT + 2;
+// at 64 x 64); five leave 22 x 22.  Where the tiles do not all run at once the
+// arithmetic counts (complex64 at 2000 x 2000, a sweep: 33 us by eights, 19 by
+// fours, 25 alone).
+constexpr int JT = 32, JT_FEW = 512, JT_NT = 512, JT_N = JT * JT / JT_NT, JT_LD = JT + 2;
 
 template <typename S>
 __global__ __launch_bounds__(JT_NT) void k_jacobi_tile(StencilGeom g, int sweeps, int tx, int ty, int nbx,
@@ -33,7 +35,7 @@ __global__ __launch_bounds__(JT_NT) void k_jacobi_tile(StencilGeom g, int sweeps
                                                        const cplx_t<S>* __restrict__ f, cplx_t<S>* uout,
                                                        double omega) {
   __shared__ cplx_t<S> buf[2][JT_LD * JT_LD];
-  const int t = threadIdx.x, lx = t & (JT - 1), ly0 = t / JT;
+  const int lx = threadIdx.x, ly0 = threadIdx.y, t = lx + JT * ly0;
   const int bx = blockIdx.x % nbx, by = blockIdx.x / nbx;
   // an axis covered by one region has no rim
   const int rx = tx == JT ? 0 : sweeps, ry = ty == JT ? 0 : sweeps;
@@ -269,7 +271,7 @@ static void jacobi_tile(const StencilGeom& g, const void* sc, const uint8_t* cod
   const int nbx = (g.nx + tx - 1) / tx, nby = (g.ny + ty - 1) / ty;
   const double n = (double)g.nx * g.ny, esz = 2.0 * sizeof(S);
   kprof_begin(KP_STENCIL, st);
-  hipLaunchKernelGGL((k_jacobi_tile<S>), dim3(nbx * nby), dim3(JT_NT), 0, st, g, sweeps, tx, ty, nbx, (const C*)sc,
+  hipLaunchKernelGGL((k_jacobi_tile<S>), dim3(nbx * nby), dim3(JT, JT_NT / JT), 0, st, g, sweeps, tx, ty, nbx, (const C*)sc,
                      code, (const C*)u, (const C*)f, (C*)unew, omega);
   kprof_end(KP_STENCIL, n * (4 * esz + 1), st);
 }
@@ -303,10 +305,17 @@ void relax_sweeps(const StencilGeom& g, const void* sc, const uint8_t* code, boo
     b = t;
   };
   if (!rbgs && g.dim == 2 && sweeps >= 2) {
-    // an even number of launches, so that the last lands in u
-    for (int launches = 2 * ((sweeps - 1) / (2 * JT_MAX) + 1); launches > 0; --launches, swap()) {
+    // Up to eight sweeps a launch on grids of at most JT_FEW tiles of 16 x 16, two to
+    // a CU (300 x 311: 1.5 us a sweep by fours and by eights), five on larger ones
+    // (500 x 500 by fours and by eights: 2.2 and 2.4 us, complex64 2.4 and 2.8; 4096
+    // x 4096: 73 and 114); a launch of one sweep is the untiled one (two sweeps at
+    // 1000 x 1000: 21 us, 30 as tiles).  An even number of launches, so that the last
+    // lands in u.
+    const int most = (size_t)((g.nx + 15) / 16) * ((g.ny + 15) / 16) <= JT_FEW ? 8 : 5;
+    for (int launches = 2 * ((sweeps - 1) / (2 * most) + 1); launches > 0; --launches, swap()) {
       const int k = (left - 1) / launches + 1;
-      jacobi_tile<S>(g, sc, code, f, a, b, omega, k, st);
+      if (k > 1) jacobi_tile<S>(g, sc, code, f, a, b, omega, k, st);
+      else stencil_jacobi<S>(g, sc, code, f, a, b, omega, st);
       left -= k;
     }
     return;
