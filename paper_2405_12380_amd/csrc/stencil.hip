@@ -514,19 +514,24 @@ void stencil_rbgs_fused(const StencilGeom& g0, const void* sc, const uint8_t* co
   if (ring) {
     // planes per workgroup: the march length (2 .. 64) with the fewest steps,
     // counting a march's prologue as three and rounds of the 512 workgroups that run
-    // at once (two per CU, by their LDS); a length from 32 on within 5% of it if there
-    // is one (the shortest).  Measured in us a sweep: 157 x 142 x 131 in fp32 15
-    // planes (one round) 46, 6 planes (three rounds) 57; fp64 200 x 180 x 160 32
-    // planes 111, 15 planes 125; 256^3 32 planes 276, 64 planes 303, 40-55 307-317;
-    // 320^3 32 planes 597, 62 planes (five marches of 62 and one of 10) 628; 384^3 55
-    // planes 962, 64 planes 980, 32 planes 1018.
+    // at once (two per CU, by their LDS).  Measured in us a sweep: 157 x 142 x 131 in
+    // fp32 15 planes (one round) 46, 6 planes (three rounds) 57; fp64 200 x 180 x 160
+    // 32 planes 104, 15 planes 114; 320^3 64 planes 521, 32 planes 531; 352^3 733 and
+    // 765; 384^3 55 planes 890, 64 planes 903, 32 planes 943.  Where one round does it
+    // all, a length from 32 on within 5% (256^3 32 planes 260, 64 planes 282, 40-55
+    // 283-303).  From five rounds of 64-plane marches on HBM is the bound, a last
+    // round that is not full costs less than more prologues, and 64 planes are best:
+    // 448^3 64 planes 1476, 32-56 planes 1544-1577; 500^3 2064 and 2111-2139; fp32
+    // 512^3 1233 and 1343.
     const long tiles = (long)((g.nx + RB_TX - 1) / RB_TX) * ((g.ny + RB_TY - 1) / RB_TY);
     auto steps = [&](int c) { return (tiles * ((g.nz + c - 1) / c) + 511) / 512 * (c + 3); };
     int zb = 2;
     for (int c = 3; c <= 64; ++c)
       if (steps(c) < steps(zb)) zb = c;
-    for (int c = 32; c < zb; ++c)
-      if (20 * steps(c) <= 21 * steps(zb)) zb = c;
+    if (steps(zb) == zb + 3)
+      for (int c = 32; c < zb; ++c)
+        if (20 * steps(c) <= 21 * steps(zb)) zb = c;
+    if (tiles * g.nz >= 64L * 2560) zb = 64;
     const long nbr = tiles * ((g.nz + zb - 1) / zb);
     hipLaunchKernelGGL((k_rbgs_ring<S, 2>), dim3((unsigned)nbr), dim3(RB_NT), 0, st, g, zb, (const C*)sc, code,
                        (const C*)uin, (const C*)f, (C*)uout, omega);
