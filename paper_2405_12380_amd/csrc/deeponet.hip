@@ -144,9 +144,12 @@ __global__ void k_branch_in_sample(SampleGrid g, const cplx_t<S>* __restrict__ r
 // the synthesis).
 constexpr int BF_K = 64;        // input entries per workgroup
 constexpr int BT_K = 16;       // weights in flight per thread of the tail
-constexpr int BT_MAXL = 12;     // layers
+constexpr int BT_MAXL = 16;     // layers
 constexpr int BT_MAXW = 1024;   // outputs of a layer
-constexpr size_t BT_BYTES = (size_t)4 << 20;  // weights after the input layer: one CU reads them
+// weights of the layers after the input layer, their columns in whole blocks of
+// 256, that one CU reads as fast as a launch or two per layer: at most so much
+// for two layers, more for each further one, and in all
+constexpr size_t BT_TWO = (size_t)4 << 20, BT_LAYER = (size_t)1 << 20, BT_ALL = (size_t)6 << 20;
 
 template <typename T>
 __global__ __launch_bounds__(512) void k_branch_first(SampleGrid g, const cplx_t<T>* __restrict__ r, size_t n,
@@ -407,17 +410,24 @@ static SampleGrid sample_grid(const don_s* net, const helm_op_s* op) {
 }
 
 // k_branch_first + k_branch_tail: layer widths within the tail's LDS, its
-// weights few enough that one CU reads them faster than a launch or two per
-// layer would take (2 MB in fp64: about 15 us)
+// weights few enough that one CU (20 us per MB) is done before the launches of
+// layer by layer (about 20 us per layer).  Whole corrections, layer by layer and
+// in two launches, us (12960 nodes, inputs 8193; MB with columns in whole blocks):
+// fp32 768-768-256 3.0 MB 116 and 93, 1024-768-256 3.8 MB 120 and 112, 900-900-256
+// 4.4 MB 116 and 124, 960-896-256 4.6 MB 114 and 128, 600-600-600-256 4.1 MB 133
+// and 112, five of 512 4.5 MB 157 and 117; fp64 768-512-256 4.0 MB 107 and 93,
+// 640-640-256 5.0 MB 99 and 107, 1024-384-256 4.8 MB 101 and 111, four of 384 5.3
+// MB 136 and 106.
 static bool branch_fits(const don_s* net) {
   const int L = (int)net->bw.size() - 1;
   size_t bytes = 0;
   if (L > BT_MAXL) return false;
   for (int l = 0; l < L; ++l) {
     if (net->bw[l + 1] > BT_MAXW) return false;
-    if (l > 0) bytes += (size_t)net->bw[l] * net->bw[l + 1] * (net->dt == HELM_C128 ? 8 : 4);
+    if (l > 0) bytes += (size_t)net->bw[l] * ((net->bw[l + 1] + 255) / 256 * 256) * (net->dt == HELM_C128 ? 8 : 4);
   }
-  return bytes <= BT_BYTES;
+  const size_t more = L > 3 ? L - 3 : 0;  // layers after the input layer and two
+  return bytes <= std::min(BT_TWO + more * BT_LAYER, BT_ALL);
 }
 
 template <typename T>
