@@ -338,14 +338,7 @@ typedef unsigned int rb_u2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rb_rsrc(const void* p, size_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off, const double2*) {
-  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
-__device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off, const float2*) {
-  const float2 v = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-  return make_double2((double)v.x, (double)v.y);
-}
-// the same with a uniform part `so` of the offset (so < the buffer's size)
+// `so`: a uniform part of the offset (so < the buffer's size)
 __device__ __forceinline__ double2 rb_ld(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned so, const double2*) {
   return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, so, 0));
 }

@@ -46,7 +46,7 @@ namespace {
 
 constexpr int TM = 128, TN = 128, BK = 64, LDSW = 72;  // tile, k step, LDS row stride (bf16, 144 B)
 
-enum { EP_F32 = 0, EP_BF16 = 1, EP_BIAS_BF16 = 2, EP_BIAS_TANH_BF16 = 3, EP_DTANH_BF16 = 4, EP_PART = 5 };
+enum { EP_F32, EP_BIAS_BF16, EP_BIAS_TANH_BF16, EP_DTANH_BF16, EP_PART };
 
 // C (M x N) = A (M x K) B (N x K)^T: both operands k-contiguous ("NT").
 struct GemmArgs {
@@ -80,10 +80,6 @@ __device__ __forceinline__ __bf16 ep_store(const GemmArgs& g, int row, int col, 
   switch (g.ep) {
     case EP_F32:
       ((float*)g.C)[o] = v;
-      break;
-    case EP_BF16:
-      r = (__bf16)v;
-      ((__bf16*)g.C)[o] = r;
       break;
     case EP_BIAS_BF16:
       r = (__bf16)(v + g.bias[col]);
@@ -403,7 +399,6 @@ __device__ __forceinline__ bf8 ld_tr(const __bf16* tile, int ld, int r, int c0, 
   const __bf16* p = tile + (r + (l >> 2)) * ld + c0 + 4 * (l & 3);
   const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p));
   const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p + 4 * ld));
-  typedef short s8 __attribute__((ext_vector_type(8)));
   return __builtin_bit_cast(bf8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
@@ -999,16 +994,13 @@ __global__ void k_f32_to_bf16(long n, const float* __restrict__ a, __bf16* __res
   for (long e = blockIdx.x * 256L + threadIdx.x; e < n; e += (long)gridDim.x * 256) b[e] = (__bf16)a[e];
 }
 
-// padded bf16 rows (ld columns) from fp32 rows (cols columns); optional transpose (ld x rows)
-__global__ void k_pad_rows(long rows, int cols, const float* __restrict__ a, int ld, __bf16* __restrict__ b,
-                           __bf16* __restrict__ bT) {
+// padded bf16 rows (ld columns) from fp32 rows (cols columns)
+__global__ void k_pad_rows(long rows, int cols, const float* __restrict__ a, int ld, __bf16* __restrict__ b) {
   const long n = rows * ld;
   for (long e = blockIdx.x * 256L + threadIdx.x; e < n; e += (long)gridDim.x * 256) {
     const long r = e / ld;
     const int c = (int)(e % ld);
-    const __bf16 v = (__bf16)(c < cols ? a[r * cols + c] : 0.0f);
-    b[e] = v;
-    if (bT) bT[(long)c * rows + r] = v;
+    b[e] = (__bf16)(c < cols ? a[r * cols + c] : 0.0f);
   }
 }
 
@@ -1426,11 +1418,7 @@ helm_status don_train_create(don_net net, const don_train_opts* o, const double*
   int maxw = 0;
   for (auto* L : {&t->bl, &t->tl})
     for (auto& y : *L) maxw = std::max(maxw, y.N);
-  size_t maxkn = 0;
-  for (auto* L : {&t->bl, &t->tl})
-    for (auto& y : *L) maxkn = std::max(maxkn, (size_t)y.Kp * y.N);
   // split-k partials: every split product runs at most 512 workgroups of 128 x 128 tiles
-  (void)maxkn;
   t->part_floats = std::max<size_t>((size_t)512 * TM * TN, (size_t)2 * S * t->p * 512);
   const size_t nch = OUT_MAXB;
   const size_t Kb = t->bl[0].Kp, Kt = t->tl[0].Kp;
@@ -1482,7 +1470,7 @@ helm_status don_train_create(don_net net, const don_train_opts* o, const double*
     for (const Layer& y : *L)
       hipLaunchKernelGGL(k_transpose, dim3(grid_for((long)y.Kp * y.N)), dim3(256), 0, t->st, y.Kp, y.N,
                          (const __bf16*)t->wbf.ptr + y.offW, (__bf16*)t->wtb.ptr + y.offW);
-  // trunk inputs: fp64 P x d -> bf16 padded rows and their transpose
+  // trunk inputs: fp64 P x d -> bf16 padded rows
   {
     Buffer tmp;
     if ((s = tmp.ensure(4 * P * t->d))) return fin(s);
@@ -1496,7 +1484,7 @@ helm_status don_train_create(don_net net, const don_train_opts* o, const double*
     e = hipMemcpy(tmp.ptr, fx.data(), sizeof(float) * fx.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
       hipLaunchKernelGGL(k_pad_rows, dim3(grid_for((long)P * Kt)), dim3(256), 0, t->st, (long)P, t->d,
-                         (const float*)tmp.ptr, (int)Kt, (__bf16*)t->X.ptr, (__bf16*)nullptr);
+                         (const float*)tmp.ptr, (int)Kt, (__bf16*)t->X.ptr);
     s = e == hipSuccess ? sync(t, "don_train_create") : hip_fail(e, "don_train_create: X");
     tmp.release();
     if (s) return fin(s);
@@ -1520,7 +1508,7 @@ helm_status don_train_data(don_trainer t, int n, const float* F, const void* Y) 
     t->step_exec = t->multi_exec = nullptr;
   }
   hipLaunchKernelGGL(k_pad_rows, dim3(grid_for((long)n * b0.Kp)), dim3(256), 0, t->st, (long)n, b0.K, F, b0.Kp,
-                     (__bf16*)t->Fdata.ptr, (__bf16*)nullptr);
+                     (__bf16*)t->Fdata.ptr);
   t->Y = (const float2*)Y;
   t->ndata = n;
   return sync(t, "don_train_data");
