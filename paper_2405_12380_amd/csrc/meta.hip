@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 
 #include "internal.h"
@@ -21,11 +22,11 @@
 namespace helm {
 
 struct Carve {
-  char* base;
+  uintptr_t base;  // 0 while only the size is wanted
   size_t off = 0;
-  explicit Carve(void* b) : base((char*)b) {}
+  explicit Carve(void* b) : base((uintptr_t)b) {}
   void* take(size_t bytes) {
-    void* p = base + off;
+    void* p = (void*)(base + off);
     off += (bytes + 255) & ~(size_t)255;
     return p;
   }
@@ -131,24 +132,33 @@ helm_status gmres_drive(helm_op_s* op, MetaCtx& c, const void* f, void* u, meta_
   const bool one_pass = o->gs_passes == 1;
   const size_t n = op->nn, esz = op_esz(op);
   const size_t fld = Carve::need(n * esz);
-  const size_t dsm = Carve::need(sizeof(double) * (2 * (size_t)(m + 1) * m + 8 * (size_t)(m + 1) + 64));
-  helm_status s = op->ws.ensure(fld * (size_t)(m + 1 + 4) + dsm + Carve::need(sizeof(GmState)));
+  char* V;
+  void *W, *z, *t;  // W: the new Arnoldi vector before normalization
+  double *H, *g, *cs, *sn, *y, *h1, *h2, *nrm;
+  GmState* gs;
+  auto carve = [&](Carve cv) -> size_t {
+    auto take_d = [&](size_t doubles) { return (double*)cv.take(sizeof(double) * doubles); };
+    const size_t m1 = (size_t)m + 1;
+    V = (char*)cv.take(fld * m1);
+    W = cv.take(n * esz);
+    z = cv.take(n * esz);
+    t = cv.take(n * esz);
+    c.r1 = cv.take(n * esz);
+    H = take_d(2 * m1 * m);
+    g = take_d(2 * m1);
+    cs = take_d(m1);
+    sn = take_d(2 * m1);
+    y = take_d(2 * m1);
+    h1 = take_d(2 * m1);
+    h2 = take_d(2 * m1);
+    nrm = take_d(8);
+    gs = (GmState*)cv.take(sizeof(GmState));
+    return cv.off;
+  };
+  // sized by the same walk that lays it out
+  helm_status s = op->ws.ensure(carve(Carve(nullptr)));
   if (s) return s;
-  Carve cv(op->ws.ptr);
-  char* V = (char*)cv.take(fld * (m + 1));
-  void* W = cv.take(n * esz);  // the new Arnoldi vector before normalization
-  void* z = cv.take(n * esz);
-  void* t = cv.take(n * esz);
-  c.r1 = cv.take(n * esz);
-  double* H = (double*)cv.take(sizeof(double) * 2 * (m + 1) * m);
-  double* g = (double*)cv.take(sizeof(double) * 2 * (m + 1));
-  double* cs = (double*)cv.take(sizeof(double) * (m + 1));
-  double* sn = (double*)cv.take(sizeof(double) * 2 * (m + 1));
-  double* y = (double*)cv.take(sizeof(double) * 2 * (m + 1));
-  double* h1 = (double*)cv.take(sizeof(double) * 2 * (m + 1));
-  double* h2 = (double*)cv.take(sizeof(double) * 2 * (m + 1));
-  double* nrm = (double*)cv.take(sizeof(double) * 8);
-  GmState* gs = (GmState*)cv.take(sizeof(GmState));
+  carve(Carve(op->ws.ptr));
   const size_t ldv = fld / esz;  // elements between basis vectors
   auto Vj = [&](int j) { return (void*)(V + (size_t)j * fld); };
 
