@@ -342,9 +342,18 @@ helm_status mg_check(const helm_op_s* op, const meta_opts* o) {
 helm_status mg_ensure(helm_op_s* op, don_s* net, const meta_opts* o, hipStream_t st) {
   Mg* m = op->mg;
   const int serial = net ? don_serial(net) : 0;
+  // trunk-basis spaces of the smoothing levels from `first` on
+  auto spaces = [&](int first) -> helm_status {
+    helm_status e = HELM_OK;
+    for (int l = first; net && l < m->levels && !e; ++l) {
+      const int pu = (size_t)o->p_used < m->ops[l]->nn ? o->p_used : (int)m->ops[l]->nn;
+      e = coarse_ensure(m->ops[l], net, pu, o->q_fp32 != 0, o->no_drop != 0, st);
+    }
+    return e;
+  };
   if (m && m->levels == o->mg_levels && m->nu == o->mg_nu && m->net_serial == serial &&
       m->ksq_version == op->ksq_version && m->p_used == o->p_used && m->dt == op->dt)
-    return HELM_OK;
+    return spaces(1);  // kept where they serve this call's options; the finest level's is the caller's
   mg_release(op);
   m = new Mg();
   op->mg = m;
@@ -374,15 +383,10 @@ helm_status mg_ensure(helm_op_s* op, don_s* net, const meta_opts* o, hipStream_t
       return s;
     }
   }
-  // trunk-basis spaces of the smoothing levels
-  if (net)
-    for (int l = 0; l < m->levels; ++l) {
-      const int pu = (size_t)o->p_used < m->ops[l]->nn ? o->p_used : (int)m->ops[l]->nn;
-      if ((s = coarse_ensure(m->ops[l], net, pu, o->q_fp32 != 0, o->no_drop != 0, st))) {
-        mg_release(op);
-        return s;
-      }
-    }
+  if ((s = spaces(0))) {
+    mg_release(op);
+    return s;
+  }
   // coarsest inverse
   helm_op_s* cop = m->ops[m->levels];
   m->nc = (int)cop->nn;
