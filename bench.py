@@ -692,6 +692,10 @@ def stencil_bandwidth(helm, I, torch, dev, N, reps=40):
         us = 1e3 * ms / cnt   # one launch per run and sweep, or per pair of Jacobi sweeps
         gbs = by[name] * nn / (us * 1e-6) / 1e9
         out[name] = {"us": round(us, 1), "GBps": round(gbs, 1), "frac_peak": round(gbs / HBM_PEAK_GBS, 3)}
+    # not comparable with records whose "jacobi" ran sweeps in pairs (193 us at
+    # 256^3 where this is 217 with the same kernel): here the copy that an odd
+    # count of sweeps ends in runs between two sweeps, outside the events
+    out["jacobi"]["note"] = "one sweep per call, a copy of u between sweeps (not timed)"
     # copy ceiling: the library's non-temporal streaming copy of 2 GiB (read +
     # write), timed with events on the stream it runs on
     buf = torch.empty(2 * 1024 ** 3 // 16, dtype=torch.complex128, device=dev)

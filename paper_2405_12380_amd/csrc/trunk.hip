@@ -8,10 +8,14 @@
 // fp64 units, the activation's vector arithmetic.  Layer by layer, with a
 // 128 x 128 tile staged through LDS in 16-deep chunks, the products ran at 41
 // of the 78.6 TFLOP/s peak: two barriers per chunk, and every activation value
-// stored to and loaded from memory.  Measured (3-256x4-128 trunk): 10.19 ->
-// 7.07 ms at 96^3 (58 TFLOP/s; the library's fp64 product of two 8192 x 8192
-// matrices reaches 71), 299 -> 157 us at 24 x 20 x 27, 279 -> 50 us at
-// 15 x 17 x 13, where most CUs had no tile.
+// stored to and loaded from memory.  Measured (3-256x4-128 trunk): 10.13 ->
+// 7.05 ms at 96^3 (58 TFLOP/s; the library's fp64 product of two 8192 x 8192
+// matrices reaches 71), 287 -> 136 us at 24 x 20 x 27, 274 -> 41 us at
+// 15 x 17 x 13, where most CUs had no tile; 3-32-32-16 at 96^3 731 -> 384 us.
+// Splitting the products into exact int8 digit products is faster at 256 wide
+// (5.7 ms), but its digits are relative to a node's largest activation and a
+// column's largest weight: a column whose weights meet only small
+// activations loses them, which neither shows alone.
 #include "common.h"
 #include "dense.h"
 #include "dense_dev.h"
@@ -153,7 +157,7 @@ void trunk_fused(int dim, const int n[3], int L, const int* w, const double* con
   // 32-row blocks, two to a CU so that one's activations run beside the
   // other's products (96^3: 7.2 ms, against 7.7 ms for 64-row blocks, one to
   // a CU); grids that would give some of the 256 CUs no 32-row block take
-  // 16-row blocks (3315 nodes: 50 us)
+  // 16-row blocks (3315 nodes: 41 us)
   if (a.nn > 256 * 32) trunk_launch<2, T>(a, out, st);
   else trunk_launch<1, T>(a, out, st);
   kprof_end(KP_MFMA, flops, st);
